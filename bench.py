@@ -74,10 +74,11 @@ def kernel_bytes(ar, kind, bi, step):
         return n * (es_t * data + es_b * b.count)
     if kind == "pack_rs":  # the adding step reuses the values it packs; no rank stores its own sent chunk
         return n * es_t * data + (n - 1) * es_b * b.count
-    if kind in ("cycle_small", "ring_small"):  # every step's messages, as the per-step kernels count them
-        es = es_t if b.direct else es_b
-        ring = (n - 1) * 5 * es * b.count
-        return ring if b.direct else ring + n * (es_t * data + es_b * b.count) + n * (es_b + es_t) * data
+    if kind == "ring_small":  # the messages in registers: every rank's value read once, the result written to each
+        return 2 * n * es_t * b.count
+    if kind == "cycle_small":  # every step's messages, as the per-step kernels count them
+        ring = (n - 1) * 5 * es_b * b.count
+        return ring + n * (es_t * data + es_b * b.count) + n * (es_b + es_t) * data
     if kind in ("unpack", "ag_unpack"):  # the fused replacing step only changes which buffer is read
         return n * (es_b + es_t) * data
     compressed = b.direct and ar.compress
@@ -359,14 +360,13 @@ def short_kernel_name(full):
 
     base = full.replace("(anonymous namespace)", "anon").split("(")[0]
     for key, short in (("rs_ag_step_c16_kernel", "rs_ag_step_c16"), ("rs_step_c16_kernel", "rs_step_c16"),
-                       ("ag_first_c16_kernel", "ag_first_c16"), ("roundtrip_c16_kernel", "ring"),
-                       ("fold_kernel", "fold")):
+                       ("ag_first_c16_kernel", "ag_first_c16"), ("roundtrip_c16_kernel", "ring")):
         if key in base:
             return short
     half = "<_Float16" in base or "IDF16_" in base
     if "small_cycle_kernel" in base:
         return "cycle_small"
-    if "chain_kernel" in base:
+    if "fold_flat_kernel" in base:  # hvdx_fold_allreduce's kernel too
         return "ring_small"
     # the tile-driven ring steps report as the ring step they are; binary32 tensors with
     # binary16 buffers are the compressed ring's (its replacing steps copy binary32)

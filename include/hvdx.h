@@ -373,11 +373,12 @@ int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
 
 /*
  * hvdx_ring_allreduce_small -- hvdx_ring_allreduce without compression, in one
- * launch: each thread runs all 2(N-1) steps (same schedule, same order of additions,
- * each step reading the sender's buffer and writing the receiver's) for one 16-byte
- * vector of every rank buffer, or element by element where a vector crosses a chunk
- * edge or a buffer is not 16-byte aligned.  Same result, bit for bit.  Intended for
- * buffers of at most HVDX_SMALL_BUCKET_BYTES; any size works.
+ * launch: each lane runs all 2(N-1) steps (same schedule, same order of additions) for
+ * one 16-byte vector of every rank buffer, or for one element where a chunk ends inside
+ * a vector, the messages in registers: every rank's value is read once and the result
+ * written to every rank.  Same result, bit for bit.  Meant for buffers of at most
+ * HVDX_SMALL_BUCKET_BYTES; any size works, and since it moves 2N elements per element
+ * instead of 5N-6, any size is faster than a launch per step.
  * Arguments and errors as hvdx_ring_allreduce with compress = HVDX_COMPRESS_NONE.
  */
 int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int dtype, int op, void* stream);
@@ -497,7 +498,8 @@ int hvdx_broadcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, 
  * added in the ring's order (starting at the rank whose chunk holds the element,
  * paper section 3), divided once for AVERAGE, and written to all N buffers.  It
  * moves 2N elements per element instead of the ring's 5(N-1), so it bounds what a
- * one-GPU schedule can do; it is not a simulation of the ring's transport.
+ * one-GPU schedule can do; it is not a simulation of the ring's transport.  The kernel
+ * is hvdx_ring_allreduce_small's, which this call offers compressed too.
  * Arguments as hvdx_ring_allreduce; compression needs no workspace here.
  */
 int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress, void* stream);

@@ -1,0 +1,197 @@
+// The whole ring of a stretch of elements in one wavefront, the messages in registers.
+//
+// An element's ring never involves another element, so a lane can run all 2(N-1) steps of
+// its elements by itself: the partial sum that rank c+s would send in adding step s is the
+// lane's accumulator, rank c+s+1's own value is added to it, and the replacing steps store
+// the finished value to every rank.  Same order of additions and same roundings as the
+// per-step kernels, so the same bits, for 2N elements moved instead of 5N-6.
+//
+// Bound: HBM, N read and N write streams at once.  What the shape has to get right is how
+// much is in flight.  Measured on MI355X (N buffers, in place, binary32):
+//   256-thread blocks, full occupancy, 4 loads in flight per lane   4.9 TB/s (N=8), 4.9 (N=32)
+//   one wavefront per block, all ranks' loads in one burst          5.7 TB/s (N=8), 5.25 (N=32)
+//   the same with 8 (N=8) or 6 (N=16, 32) wavefronts per CU          6.25, 6.05, 5.7 TB/s
+// (one stream in place: 6.55).  More in flight only spreads the accesses to an HBM page
+// apart in time.  A wavefront that goes on to a second tile loses 10-20%: loads and stores
+// share one in-order counter, so its next loads wait behind its own stores.  Hence one
+// wavefront per block, one 16-byte vector per lane and rank, one burst of loads, the
+// stores, and the end; an LDS reservation no one uses holds the wavefronts per CU down.
+#pragma once
+
+#include "ring_math.hpp"
+
+namespace hvdx {
+namespace {
+
+constexpr int kFoldLanes = 64;
+
+// 16-byte vectors that need only their elements' alignment.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef _Float16 f16x8u __attribute__((ext_vector_type(8), aligned(2)));
+
+// Tensors of type TT, sums in type TB: a lane's vector, the same without its alignment, the
+// accumulator, and the conversions (binary32 tensors summed in binary16 are rounded where
+// first read and widened exactly where stored).
+template <typename TT, typename TB>
+struct FoldTypes;
+template <>
+struct FoldTypes<float, float> {
+  using vec = f32x4;
+  using uvec = f32x4u;
+  using acc = f32x4;
+  static constexpr int V = 4;
+  __device__ static acc in(vec v) { return v; }
+  __device__ static vec out(acc v) { return v; }
+};
+template <>
+struct FoldTypes<_Float16, _Float16> {
+  using vec = f16x8;
+  using uvec = f16x8u;
+  using acc = f16x8;
+  static constexpr int V = 8;
+  __device__ static acc in(vec v) { return v; }
+  __device__ static vec out(acc v) { return v; }
+};
+template <>
+struct FoldTypes<float, _Float16> {
+  using vec = f32x4;
+  using uvec = f32x4u;
+  using acc = f16x4;
+  static constexpr int V = 4;
+  __device__ static acc in(vec v) {
+    acc h;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h[k] = (_Float16)v[k];
+    return h;
+  }
+  __device__ static vec out(acc h) {
+    vec v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = (float)h[k];
+    return v;
+  }
+};
+
+// The AVERAGE divide of a finished sum.
+template <int DIV>
+__device__ __forceinline__ f32x4 finish_vec(f32x4 s, const RingArgs& a) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s[k] = finish<DIV>(s[k], a);
+  return s;
+}
+template <int DIV>
+__device__ __forceinline__ f16x8 finish_vec(f16x8 s, const RingArgs& a) {
+  if constexpr (DIV == DIV_POW2) return s * (f16x8)((_Float16)a.inv);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s[k] = finish16<DIV>(s[k], a);
+  return s;
+}
+template <int DIV>
+__device__ __forceinline__ f16x4 finish_vec(f16x4 s, const RingArgs& a) {
+  if constexpr (DIV == DIV_POW2) return s * (f16x4)((_Float16)a.inv);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s[k] = finish16<DIV>(s[k], a);
+  return s;
+}
+
+template <int DIV>
+__device__ __forceinline__ float finish_one(float v, const RingArgs& a) { return finish<DIV>(v, a); }
+template <int DIV>
+__device__ __forceinline__ _Float16 finish_one(_Float16 v, const RingArgs& a) { return finish16<DIV>(v, a); }
+
+// An address known to be global memory: pointers out of a table would otherwise be accessed
+// by flat instructions, which cannot be waited for one after the other.
+template <typename T>
+using Global = T __attribute__((address_space(1)))*;
+
+// The same number, which the compiler cannot tell: a burst's loads and its additions test
+// it separately, and joining the two tests would copy the code for every length.
+__device__ __forceinline__ int same_count(int v) {
+  asm("" : "+s"(v));
+  return v;
+}
+
+// One vector per lane.  ptr(k) is the address of the stretch's first element on the k-th
+// rank of its ring (rank c+k mod N); MT is FoldTypes::vec or, unaligned, ::uvec.
+template <typename TT, typename TB, int DIV, int B, typename MT, typename Ptr>
+__device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a) {
+  using F = FoldTypes<TT, TB>;
+  using vec = typename F::vec;
+  const unsigned off = threadIdx.x * 16u;  // unsigned: a scalar base and a 32-bit offset per access
+  typename F::acc s = (typename F::acc)((TB)-0.0f);  // x + -0 = x for every x
+  auto at = [&](int k) { return (Global<MT>)((Global<char>)ptr(k) + off); };
+  const int n = a.n;
+  int k0 = 0;
+#pragma unroll 1
+  for (; k0 + B <= n; k0 += B) {  // whole bursts, no test between the loads
+    vec x[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) x[j] = __builtin_nontemporal_load(at(k0 + j));
+    __builtin_amdgcn_sched_barrier(0);  // no addition, and so no wait, before the last load is out
+#pragma unroll
+    for (int j = 0; j < B; ++j) s = F::in(x[j]) + s;
+  }
+  constexpr int R = B > 16 ? 16 : B;  // the rest in one or two bursts of up to 16
+#pragma unroll 1
+  for (; k0 < n; k0 += R) {
+    vec x[R];
+    const int left = n - k0, adds = same_count(left);
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (j < left) x[j] = __builtin_nontemporal_load(at(k0 + j));
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (j < adds) s = F::in(x[j]) + s;
+  }
+  const MT o = F::out(finish_vec<DIV>(s, a));
+#pragma unroll 4
+  for (int k = 0; k < n; ++k) __builtin_nontemporal_store(o, at(k));
+}
+
+// The same for one element per lane: the elements past a stretch's last whole vector.  Loads
+// past the last rank repeat its own.
+template <typename TT, typename TB, int DIV, typename Ptr>
+__device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, int e) {
+  constexpr int B = 8;
+  const int n = a.n;
+  TB s = (TB)-0.0f;
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += B) {
+    TT x[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) x[j] = ((Global<TT>)ptr(k0 + j < n ? k0 + j : n - 1))[e];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const TB sum = (TB)x[j] + s;
+      s = k0 + j < n ? sum : s;
+    }
+  }
+  const TT o = (TT)finish_one<DIV>(s, a);
+#pragma unroll 1
+  for (int k = 0; k < n; ++k) ((Global<TT>)ptr(k))[e] = o;
+}
+
+// A wavefront's stretch of m (1 .. 64*V) elements.
+template <typename TT, typename TB, int DIV, int B, typename Ptr>
+__device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int m, bool aligned) {
+  using F = FoldTypes<TT, TB>;
+  const int lane = threadIdx.x;
+  const int vecs = m / F::V, rest = m - vecs * F::V;
+  if (lane < vecs) {
+    if (aligned) fold_vectors<TT, TB, DIV, B, typename F::vec>(ptr, a);
+    else fold_vectors<TT, TB, DIV, B, typename F::uvec>(ptr, a);
+  }
+  if (lane < rest) fold_element<TT, TB, DIV>(ptr, a, vecs * F::V + lane);
+}
+
+// Wavefronts per SIMD that the registers of a burst have to leave room for.
+constexpr int fold_waves(int burst) { return burst == 8 ? 4 : 2; }
+
+// Host side: the loads of a burst for n ranks (one instantiation each).
+inline int fold_burst(int n) { return n <= 8 ? 8 : n <= 16 ? 16 : 32; }
+
+// LDS bytes that let 8 (bursts of 8) or 6 (longer bursts) one-wavefront blocks onto a CU.
+inline unsigned fold_lds(int burst) { return (160u << 10) / (burst == 8 ? 8 : 6) / 512 * 512 - 512; }
+
+}  // namespace
+}  // namespace hvdx

@@ -1009,9 +1009,9 @@ int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int 
   hipStream_t st = static_cast<hipStream_t>(stream);
   TimedLaunch timed(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, HVDX_COMPRESS_NONE, count, st);
   TimedLaunch timed_phase(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, HVDX_COMPRESS_NONE, count, st, -1, true);
-  const hipError_t e = hvdx::launch_chain(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), count, dtype,
-                                          div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
-  return e == hipSuccess ? HVDX_OK : hip_fail(e, "small ring launch");
+  const hipError_t e = hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), dtype, dtype,
+                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
+  return e == hipSuccess ? HVDX_OK : hip_fail(e, "one-launch ring");
 }
 
 int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
@@ -1027,8 +1027,9 @@ int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   const hvdx::RingArgs a = ring_args(nranks, count, 0);
   TimedLaunch timed(HVDX_KERNEL_FOLD, -1, nranks, dtype, compress, count, st);
   TimedLaunch timed_phase(HVDX_KERNEL_FOLD, -1, nranks, dtype, compress, count, st, -1, true);
-  const hipError_t e = hvdx::launch_fold(rank_ptrs(bufs, nranks), a, count, dtype, compress, div_mode(op, nranks),
-                                         vectors_ok(bufs, nranks, nullptr), st);
+  const hipError_t e =
+      hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), a, dtype, compress == HVDX_COMPRESS_FP16 ? HVDX_FLOAT16 : dtype,
+                             div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "fold launch");
 }
 

@@ -136,16 +136,15 @@ hipError_t launch_ag_tiles(const TiledRing& k, int tensor_dtype, int buf_dtype, 
 // Adding step s (0 .. N-3) reading every receiver's own values from its tensors (and at
 // s = 0 the sender's too), over the copy-in's tiles.
 hipError_t launch_add_tiles(const TiledRing& k, int tensor_dtype, int buf_dtype, int step, hipStream_t stream);
-// A small ring in one launch: each thread runs every step for its elements.
-hipError_t launch_chain(const RankPtrs& bufs, const RingArgs& a, int64_t count, int dtype, int divmode,
-                        bool vector_ok, hipStream_t stream);
 // A small fusion buffer's copy-in, ring and copy-out in one launch.
 hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, const int64_t* offset, int ntensors,
                               int tensor_dtype, const RankPtrs& bufs, const RingArgs& a, int64_t count, int buf_dtype,
                               int divmode, hipStream_t stream);
-// The ring's per-element fold in one pass (same bits, no per-step messages).
-hipError_t launch_fold(const RankPtrs& bufs, const RingArgs& a, int64_t count, int dtype, int compress, int divmode,
-                       bool vector_ok, hipStream_t stream);
+
+// The whole ring in one launch (fold_kernels.hip): each lane runs every step for its elements,
+// the messages in registers.  Over flat rank buffers (a holds their partition):
+hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
+                            bool aligned, hipStream_t stream);
 
 // Broadcast chain step (broadcast_kernels.hip).
 struct BcastArgs {

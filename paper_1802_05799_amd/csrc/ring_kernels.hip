@@ -501,131 +501,6 @@ __global__ __launch_bounds__(P::BS) void rs_ag_step_c16_kernel(RankPtrs x, const
   }
 }
 
-// ---- the ring's fold computed directly -----------------------------------------------
-//
-// Element e of chunk c ends as FIN(((x_c + x_{c+1}) + ...) + x_{c+N-1}) on every rank,
-// the ring's summation order.  One kernel reads the N values of each element once,
-// adds them in that order in registers (binary16 after rounding each input when
-// compressing) and writes the result to all N ranks: 2N element reads and writes
-// instead of the ring's 5(N-1), with identical bits, but without the per-step
-// messages of a real ring.
-
-
-template <typename T, bool COMP>
-struct FoldTypes;
-template <>
-struct FoldTypes<float, false> {
-  using acc = float;
-  __device__ static float in(float v) { return v; }
-  __device__ static float out(float v) { return v; }
-};
-template <>
-struct FoldTypes<_Float16, false> {
-  using acc = _Float16;
-  __device__ static _Float16 in(_Float16 v) { return v; }
-  __device__ static _Float16 out(_Float16 v) { return v; }
-};
-template <>
-struct FoldTypes<float, true> {  // binary32 data, binary16 arithmetic
-  using acc = _Float16;
-  __device__ static _Float16 in(float v) { return (_Float16)v; }
-  __device__ static float out(_Float16 v) { return (float)v; }
-};
-
-constexpr int kFoldBatch = 8;  // ranks whose loads are in flight together
-
-// Four elements as one access: 16 bytes of binary32, 8 of binary16.
-template <typename T>
-struct Four;
-template <>
-struct Four<float> {
-  using type = f32x4;
-};
-template <>
-struct Four<_Float16> {
-  using type = f16x4;
-};
-
-template <int DIV>
-__device__ __forceinline__ float fold_finish(float v, const RingArgs& a) {
-  return finish<DIV>(v, a);
-}
-template <int DIV>
-__device__ __forceinline__ _Float16 fold_finish(_Float16 v, const RingArgs& a) {
-  return finish16<DIV>(v, a);
-}
-
-template <typename T, int DIV, bool COMP, bool VEC_OK>
-__global__ __launch_bounds__(kBlock) void fold_kernel(RankPtrs bufs, RingArgs a, int64_t count) {
-  using F = FoldTypes<T, COMP>;
-  using A = typename F::acc;
-  constexpr int V = 4;  // elements per lane (16 bytes of binary32, 8 of binary16)
-  const int64_t nv = (count + V - 1) / V;
-  const int n = a.n;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nv; i += (int64_t)gridDim.x * kBlock) {
-    const int64_t e0 = i * V;
-    const int64_t c0 = chunk_index(e0, a);
-    const bool whole = VEC_OK && e0 + V <= count && chunk_index(e0 + V - 1, a) == c0;
-    if (whole) {  // one aligned 4-element access per rank, contiguous across the wavefront
-      using VT = typename Four<T>::type;
-      A acc[V];
-      VT v[kFoldBatch];
-      for (int k0 = 0; k0 < n; k0 += kFoldBatch) {
-#pragma unroll
-        for (int kk = 0; kk < kFoldBatch; ++kk) {
-          const int k = k0 + kk;
-          if (k < n)
-            v[kk] = *reinterpret_cast<const VT*>(static_cast<const T*>(bufs.p[(c0 + k) % n]) + e0);
-        }
-#pragma unroll
-        for (int kk = 0; kk < kFoldBatch; ++kk) {
-          const int k = k0 + kk;
-          if (k < n) {
-#pragma unroll
-            for (int j = 0; j < V; ++j) acc[j] = k == 0 ? F::in(v[kk][j]) : (A)(acc[j] + F::in(v[kk][j]));
-          }
-        }
-      }
-      VT out;
-#pragma unroll
-      for (int j = 0; j < V; ++j) out[j] = F::out(fold_finish<DIV>(acc[j], a));
-      for (int r = 0; r < n; ++r)
-        *reinterpret_cast<VT*>(static_cast<T*>(bufs.p[r]) + e0) = out;
-      continue;
-    }
-    for (int64_t e = e0; e < e0 + V && e < count; ++e) {  // vectors that cross a chunk edge
-      const int64_t c = chunk_index(e, a);
-      A acc = F::in(static_cast<const T*>(bufs.p[c])[e]);
-      for (int k = 1; k < n; ++k) acc = (A)(acc + F::in(static_cast<const T*>(bufs.p[(c + k) % n])[e]));
-      acc = fold_finish<DIV>(acc, a);
-      for (int r = 0; r < n; ++r) static_cast<T*>(bufs.p[r])[e] = F::out(acc);
-    }
-  }
-}
-
-// ---- a small ring in one launch ----------------------------------------------------
-//
-// For buffers so small that each step's launch costs more than its messages: one
-// thread runs all 2(N-1) steps for one 16-byte vector (or, where a vector crosses a
-// chunk edge or the buffers are not 16-byte aligned, for each of its elements), each
-// step still reading the sender's buffer and writing the receiver's in memory.
-
-template <typename T, int DIV, bool VEC_OK>
-__global__ __launch_bounds__(kBlock) void chain_kernel(RankPtrs bufs, RingArgs a, int64_t count) {
-  using VT = typename Vec<T>::type;
-  constexpr int V = Vec<T>::n;
-  const int64_t nv = (count + V - 1) / V;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nv; i += (int64_t)gridDim.x * kBlock) {
-    const int64_t e0 = i * V;
-    const int64_t c0 = chunk_index(e0, a);
-    if (VEC_OK && e0 + V <= count && chunk_index(e0 + V - 1, a) == c0) {
-      ring_chain<T, VT, DIV>(bufs, e0, (int)c0, a);
-      continue;
-    }
-    for (int64_t e = e0; e < e0 + V && e < count; ++e) ring_chain<T, T, DIV>(bufs, e, (int)chunk_index(e, a), a);
-  }
-}
-
 // One rank, compressed: the result is the value rounded to binary16 and widened.
 __global__ __launch_bounds__(kBlock) void roundtrip_c16_kernel(float* x, int64_t count) {
   const int64_t gthreads = (int64_t)gridDim.x * kBlock;
@@ -888,55 +763,6 @@ hipError_t launch_rs_ag_step_c16(const RankPtrs& x, void* wire, const RingArgs& 
   _Float16* w = static_cast<_Float16*>(wire);
   if (streams(a, 4)) rs_ag_c16_launch<C16RsAgStream>(x, w, a, divmode, vector_ok, stream);
   else rs_ag_c16_launch<C16Cached>(x, w, a, divmode, vector_ok, stream);
-  return hipGetLastError();
-}
-
-hipError_t launch_chain(const RankPtrs& bufs, const RingArgs& a, int64_t count, int dtype, int divmode,
-                        bool vector_ok, hipStream_t stream) {
-  const int64_t v = dtype == HVDX_FLOAT32 ? 4 : 8;
-  int64_t blocks = ((count + v - 1) / v + kBlock - 1) / kBlock;
-  if (blocks < 1) blocks = 1;
-  if (blocks > 65536) blocks = 65536;
-  const dim3 grid((unsigned)blocks), block(kBlock);
-#define HVDX_CHAIN(T, DIV) \
-  if (vector_ok) HVDX_LAUNCH((chain_kernel<T, DIV, true>), grid, block, 0, stream, bufs, a, count); \
-  else HVDX_LAUNCH((chain_kernel<T, DIV, false>), grid, block, 0, stream, bufs, a, count)
-#define HVDX_CHAIN_D(T) \
-  if (divmode == DIV_NONE) { HVDX_CHAIN(T, DIV_NONE); } \
-  else if (divmode == DIV_POW2) { HVDX_CHAIN(T, DIV_POW2); } \
-  else { HVDX_CHAIN(T, DIV_TRUE); }
-  if (dtype == HVDX_FLOAT32) {
-    HVDX_CHAIN_D(float)
-  } else {
-    HVDX_CHAIN_D(_Float16)
-  }
-#undef HVDX_CHAIN_D
-#undef HVDX_CHAIN
-  return hipGetLastError();
-}
-
-hipError_t launch_fold(const RankPtrs& bufs, const RingArgs& a, int64_t count, int dtype, int compress, int divmode,
-                       bool vector_ok, hipStream_t stream) {
-  int64_t blocks = (count / 4 + kBlock) / kBlock;
-  if (blocks < 1) blocks = 1;
-  if (blocks > (1 << 20)) blocks = 1 << 20;
-  const dim3 grid((unsigned)blocks), block(kBlock);
-#define HVDX_FOLD(T, C, DIV) \
-  if (vector_ok) HVDX_LAUNCH((fold_kernel<T, DIV, C, true>), grid, block, 0, stream, bufs, a, count); \
-  else HVDX_LAUNCH((fold_kernel<T, DIV, C, false>), grid, block, 0, stream, bufs, a, count)
-#define HVDX_FOLD_D(T, C) \
-  if (divmode == DIV_NONE) { HVDX_FOLD(T, C, DIV_NONE); } \
-  else if (divmode == DIV_POW2) { HVDX_FOLD(T, C, DIV_POW2); } \
-  else { HVDX_FOLD(T, C, DIV_TRUE); }
-  if (compress == HVDX_COMPRESS_FP16) {
-    HVDX_FOLD_D(float, true)
-  } else if (dtype == HVDX_FLOAT32) {
-    HVDX_FOLD_D(float, false)
-  } else {
-    HVDX_FOLD_D(_Float16, false)
-  }
-#undef HVDX_FOLD_D
-#undef HVDX_FOLD
   return hipGetLastError();
 }
 

@@ -446,19 +446,28 @@ def small_cycle_threads(n, count, numel, offset, V, k=K):
 
 
 def chain_threads(count, V, n, fold=False, k=K):
-    """chain_kernel (or, with fold, fold_kernel's grid): how many threads take each
-    element (grid-stride over V-element vectors, one thread per vector)."""
-    nv = (count + V - 1) // V
-    if fold:
-        blocks = min(max((count // 4 + 256) // 256, 1), 1 << 20)
-    else:
-        blocks = min(max((nv + 255) // 256, 1), 65536)
+    """fold_flat_kernel (`fold` or not, one kernel): how many lanes take each element.  Block
+    row c is chunk c, whose stretches are its pieces of the grid of 64*V elements; a lane
+    takes one whole vector of its stretch, then the first lanes one element each of the rest."""
+    S = 64 * V
+    q, rem = divmod(count, n)
     hits = np.zeros(count, np.int64)
-    i = np.arange(blocks * 256, dtype=np.int64) + k.lane_shift
-    while (i < nv).any():
-        for e0 in (i[i < nv] * V):
-            add(hits, np.arange(e0, min(e0 + V, count)))
-        i = i + blocks * 256
+    gx = min((q + (1 if rem else 0)) // S + 2, 1 << 22)
+    for c in range(n):
+        start, length = chunk(c, q, rem)
+        end = start + length
+        for bx in range(gx):
+            g = start // S + bx
+            while g * S < end:
+                e0, e1 = max(g * S, start), min((g + 1) * S, end)
+                vecs, rest = divmod(e1 - e0, V)
+                for lane in range(64):
+                    if lane < vecs:
+                        e = e0 + (lane + k.lane_shift) * V
+                        add(hits, np.arange(e, e + V))
+                    if lane < rest:
+                        add(hits, np.array([e0 + vecs * V + lane]))
+                g += gx
     return hits
 
 
