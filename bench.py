@@ -2,7 +2,10 @@
 
 One step = one allreduce (AVERAGE) of every rank's gradient tensors: the Tensor
 Fusion plan's copy-in, the ring's N-1 reduce-scatter and N-1 all-gather steps,
-and the copy-out, for every fusion buffer, with inputs already in GPU memory.
+and the copy-out, for every fusion buffer, with inputs already in GPU memory.  By
+default the library runs them in one launch, the messages in registers; the same
+allreduce with a launch per ring step is timed beside it (`ring_roofline`,
+`fusion_buffer_modes`).
 The metric is algorithm bandwidth: one rank's fp32 gradient bytes / step time.
 
     python bench.py [--steps K] [--warmup W] [--workload vgg16] [--no-per-config]
@@ -13,7 +16,8 @@ sets are several times the 256 MB Infinity Cache.  Besides the headline workload
 reports, per workload, the step time and the per-kernel time split measured with
 HIP events; the roofline object is for the kernel with the largest share of the
 step (HBM-bound: achieved algorithmic bytes / time against the 8 TB/s peak), and
-`ring_roofline` the same for the ring's adding and replacing step kernels together.
+`ring_roofline` the same for the ring's adding and replacing step kernels together,
+run in launches of their own.
 `cpu_baseline` times the C oracle on the same whole workload on this host's cores.
 """
 from __future__ import annotations
@@ -32,6 +36,8 @@ TILED_REPLACE_IN_TENSORS, TILED_ADD_FROM_TENSORS = 1, 2  # the HVDX_TILED_* bits
 # FusedAllreduce arguments of each way of running the fusion buffers
 BUFFER_MODES = {"ring_on_tensors": {}, "copy_in": {"add_from_tensors": False},
                 "paper_copies": {"replace_in_tensors": False}}
+# ... and what makes the default run the ring's steps in launches of their own (buckets of a few MiB excepted)
+PER_STEP = {"small_bucket_bytes": (4 << 20) - 1}
 
 
 def parse():
@@ -74,11 +80,8 @@ def kernel_bytes(ar, kind, bi, step):
         return n * (es_t * data + es_b * b.count)
     if kind == "pack_rs":  # the adding step reuses the values it packs; no rank stores its own sent chunk
         return n * es_t * data + (n - 1) * es_b * b.count
-    if kind == "ring_small":  # the messages in registers: every rank's value read once, the result written to each
-        return 2 * n * es_t * b.count
-    if kind == "cycle_small":  # every step's messages, as the per-step kernels count them
-        ring = (n - 1) * 5 * es_b * b.count
-        return ring + n * (es_t * data + es_b * b.count) + n * (es_b + es_t) * data
+    if kind in ("cycle_small", "ring_small"):  # the messages in registers: every value read once, written once
+        return 2 * n * es_t * data
     if kind in ("unpack", "ag_unpack"):  # the fused replacing step only changes which buffer is read
         return n * (es_b + es_t) * data
     compressed = b.direct and ar.compress
@@ -116,8 +119,8 @@ KIND_CODE = {"pack": 0, "rs": 1, "ag": 2, "unpack": 3, "ring": 4, "rs_ag": 6, "f
 
 def kernel_name(ar, kind, bi):
     b = ar.buckets[bi[0] if isinstance(bi, tuple) else bi]
-    if kind in ("cycle_small", "ring_small"):
-        return kind
+    if kind in ("cycle_small", "ring_small"):  # of the fusion buffers, of the direct tensors: one kernel
+        return "whole_ring"
     if kind in ("rs", "ag", "rs_ag"):
         flags = 0 if b.direct else ar.tiled_flags
         # a compressed bucket's steps that read or write binary32 tensors are the compressed ring's
@@ -366,8 +369,8 @@ def short_kernel_name(full):
     half = "<_Float16" in base or "IDF16_" in base
     if "small_cycle_kernel" in base:
         return "cycle_small"
-    if "fold_flat_kernel" in base:  # hvdx_fold_allreduce's kernel too
-        return "ring_small"
+    if "fold_table_kernel" in base or "fold_flat_kernel" in base:
+        return "whole_ring"
     # the tile-driven ring steps report as the ring step they are; binary32 tensors with
     # binary16 buffers are the compressed ring's (its replacing steps copy binary32)
     mixed = re.search(r"tiles_kernel<float, _Float16", base) or re.search(r"tiles_kernelIfDF16_", base)
@@ -668,38 +671,47 @@ def main():
                 print(f"# {name}: {r['ms_per_step']:.3f} ms/step, {r['algbw_GBps']:.1f} GB/s, "
                       f"graph {r['graph_ms_per_step']:.3f} ms/step", file=sys.stderr,
                       flush=True)
-            ring_frac, path_frac = hbm_fracs(r)
+            _, path_frac = hbm_fracs(r)
+            per_step = measure(name, max(3, args.steps // 2), 2, graph_pass=False, **PER_STEP)
+            ring_frac, _ = hbm_fracs(per_step)
             # the same allreduce started with the Infinity Cache flushed
             f = measure(name, max(3, args.steps // 2), 1, graph_pass=False, flush_bytes=MALL_FLUSH_BYTES)
-            f_ring, f_path = hbm_fracs(f)
+            _, f_path = hbm_fracs(f)
+            fs = measure(name, max(3, args.steps // 2), 1, graph_pass=False, flush_bytes=MALL_FLUSH_BYTES, **PER_STEP)
+            f_ring, _ = hbm_fracs(fs)
             print(f"# {name} (cache flushed): {f['ms_per_step']:.3f} ms/step, ring {f_ring}", file=sys.stderr,
                   flush=True)
             per_config[name] = {
                 "nranks": r["nranks"],
                 "ms_per_step": round(r["ms_per_step"], 4),
                 "graph_ms_per_step": r["graph_ms_per_step"] and round(r["graph_ms_per_step"], 4),
-                # algorithmic bytes over time: the ring's kernels alone, and the whole step
+                # algorithmic bytes over time: the ring's step kernels alone, and the whole (one-launch) step
+                "per_step_ms": round(per_step["ms_per_step"], 4),
                 "ring_hbm_frac": ring_frac,
                 "path_hbm_frac": path_frac,
                 "mall_flushed": {"ms_per_step": round(f["ms_per_step"], 4),
                                  "algbw_GBps": round(f["algbw_GBps"], 2),
                                  "ring_hbm_frac": f_ring, "path_hbm_frac": f_path,
                                  "kernels_hbm_frac": {k: v["hbm_frac"] and round(v["hbm_frac"], 4)
-                                                      for k, v in f["kernels"].items()}},
+                                                      for x in (f, fs) for k, v in x["kernels"].items()}},
                 "algbw_GBps": round(r["algbw_GBps"], 2),
                 "busbw_GBps": round(r["busbw_GBps"], 2),
                 "kernels": {k: {"avg_us": round(v["avg_us"], 2), "GBps": v["GBps"] and round(v["GBps"], 1),
                                 "hbm_frac": v["hbm_frac"] and round(v["hbm_frac"], 4),
                                 "share": round(v["share"], 4)} for k, v in r["kernels"].items()},
+                "step_kernels": {k: {"avg_us": round(v["avg_us"], 2), "GBps": v["GBps"] and round(v["GBps"], 1),
+                                     "hbm_frac": v["hbm_frac"] and round(v["hbm_frac"], 4),
+                                     "share": round(v["share"], 4)} for k, v in per_step["kernels"].items()},
             }
 
-    # the fusion buffers' ring on the tensors (the default) against the paper's copies: the
-    # copy-in kept (fused with adding step 0), and the whole ring in the buffers between
+    # one launch (the default), then the steps in launches of their own: the fusion buffers' ring on
+    # the tensors, and the paper's copies: the copy-in kept (fused with adding step 0), and the whole ring in the buffers between
     # the copy-in and the copy-out (fused with the first and last steps); same bits
     buffer_modes = {}
     if not args.no_per_config:
         for name in ("resnet50", "inceptionv3", "vgg16", "vgg16fp16"):
-            row = {"ring_on_tensors_ms": per_config[name]["ms_per_step"]}
+            row = {"one_launch_ms": per_config[name]["ms_per_step"],
+                   "ring_on_tensors_ms": per_config[name]["per_step_ms"]}
             for key, kw in (("copy_in_ms", BUFFER_MODES["copy_in"]), ("paper_copies_ms", BUFFER_MODES["paper_copies"])):
                 r = measure(name, max(3, args.steps // 2), 2, per_kernel_pass=False, graph_pass=False, **kw)
                 row[key] = round(r["ms_per_step"], 4)
@@ -753,9 +765,11 @@ def main():
         "timing_outlier_samples": head["timing_outliers"],
         "algorithmic_bytes_per_step": dom["bytes"] // args.steps,
     }
-    # the ring's own step kernels (adding, replacing, and the fused boundary step), all
-    # launches together: their algorithmic bytes over their summed kernel time
-    ring_k = {k: v for k, v in head["kernels"].items() if k.startswith(("rs_step", "ag_step", "rs_ag_step"))}
+    # the ring's own step kernels (adding, replacing, and the fused boundary step) in launches of
+    # their own, all together: their algorithmic bytes over their summed kernel time
+    steps = measure(args.workload, args.steps, args.warmup, graph_pass=False,
+                    **{**PER_STEP, **BUFFER_MODES[args.fusion_buffer_mode]})
+    ring_k = {k: v for k, v in steps["kernels"].items() if k.startswith(("rs_step", "ag_step", "rs_ag_step"))}
     ring_bytes = sum(v["bytes"] for v in ring_k.values()) // args.steps
     ring_ms = sum(v["ms_per_step"] for v in ring_k.values())
     ring_roofline = {
@@ -767,6 +781,7 @@ def main():
         "frac": round(ring_bytes / (ring_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if ring_ms else None,
         "launches_per_step": sum(v["launches"] for v in ring_k.values()) // args.steps,
         "kernel_ms_per_step": round(ring_ms, 4),
+        "ms_per_step": round(steps["ms_per_step"], 4),
         "algorithmic_bytes_per_step": ring_bytes,
     }
     out = {
@@ -787,9 +802,10 @@ def main():
             "simulated_ranks": head["nranks"],
             "op": "average",
             "fusion_threshold_bytes": 64 << 20,
-            # adding steps read each rank's own elements from its tensors, partial sums in the
-            # fusion buffers, replacing steps write the tensors (fusion_buffer_modes: the others)
+            # adding steps read each rank's own elements from its tensors, replacing steps write the
+            # tensors; in one launch no message passes through memory (fusion_buffer_modes: the others)
             "fusion_buffer_mode": args.fusion_buffer_mode,
+            "one_launch": args.fusion_buffer_mode == "ring_on_tensors",
             "buckets": head["buckets"],
         },
         "busbw_GBps": round(head["busbw_GBps"], 2),

@@ -315,6 +315,45 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
                               int nranks, int op, int flags, void* stream);
 
 /*
+ * hvdx_fuse_cycle -- the whole cycles of any number of fusion buffers in one launch: every
+ * tensor ends, bit for bit, as hvdx_fuse_allreduce on its buffer leaves it.  No fusion
+ * buffer is used: an element's ring never involves another element, so a lane takes its
+ * elements from every rank's tensor, runs all 2(N-1) steps of the ring in their order with
+ * the messages in registers (binary16 ones when compressing), and stores the result to every
+ * rank's tensor: 2N elements moved per element, whatever the size.  A tensor reduced by
+ * itself is a buffer of one tensor.
+ *
+ * hvdx_fuse_cycle_table -- host only: the table that drives it, for copying to the GPU.
+ *   tensors[nranks*ntensors]  HOST array of device pointers, rank-major (entry r*ntensors + t),
+ *                             aligned to their elements; the ranks' tensors must not overlap
+ *   numel, offset[ntensors]   host, elements of each tensor and its start in its buffer
+ *   bucket_of[ntensors]       host, its buffer, 0 .. nbuckets-1
+ *   bucket_count[nbuckets]    host, elements of each buffer (as produced by hvdx_fuse_plan):
+ *                             what its ring's chunks are cut from
+ *   table                     host memory of `capacity` bytes, 16-byte aligned, or NULL for
+ *                             a capacity (and a tile count) that is enough
+ *   ntiles                    out: tiles in the table
+ * Returns the table's bytes, or a negative HVDX_ERR_* (HVDX_ERR_WORKSPACE when capacity is too
+ * small).  The table holds the tensors' addresses and belongs to these types and nranks.
+ *
+ * hvdx_fuse_cycle:
+ *   table      DEVICE copy of the table, 16-byte aligned (not checked: other contents make
+ *              the kernel read or write outside the tensors)
+ *   ntiles     <= HVDX_CYCLE_MAX_TILES
+ *   count      the buffers' elements, for the timeline's record
+ *   direct     1 when every buffer is a tensor reduced by itself: the timeline then says so
+ * Errors: HVDX_ERR_INVALID, HVDX_ERR_UNSUPPORTED (binary16 tensors with a binary32 buffer, too
+ * many tiles), HVDX_ERR_HIP.
+ */
+#define HVDX_CYCLE_MAX_TILES (1LL << 34)
+int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const int64_t* offset,
+                              const int32_t* bucket_of, const int64_t* bucket_count, int ntensors, int nbuckets,
+                              int tensor_dtype, int buf_dtype, int nranks, void* table, int64_t capacity,
+                              int64_t* ntiles);
+int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t count, int tensor_dtype, int buf_dtype,
+                    int nranks, int op, int direct, void* stream);
+
+/*
  * hvdx_fuse_allreduce_small -- hvdx_fuse_allreduce for small fusion buffers: the same
  * result, bit for bit, in one kernel launch instead of 2N-1.  Each thread takes a
  * 16-byte stretch of the buffer (element by element where it meets a tensor edge)

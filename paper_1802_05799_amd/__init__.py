@@ -52,6 +52,8 @@ from ._lib import (  # noqa: F401
     COPY_IN,
     COPY_OUT,
     hvdx_fuse_allreduce_small,
+    hvdx_fuse_cycle,
+    hvdx_fuse_cycle_table,
     hvdx_fuse_pack,
     hvdx_fuse_pack_rs,
     hvdx_fuse_plan,

@@ -10,7 +10,7 @@
 // much is in flight.  Measured on MI355X (N buffers, in place, binary32):
 //   256-thread blocks, full occupancy, 4 loads in flight per lane   4.9 TB/s (N=8), 4.9 (N=32)
 //   one wavefront per block, all ranks' loads in one burst          5.7 TB/s (N=8), 5.25 (N=32)
-//   the same with 8 (N=8) or 6 (N=16, 32) wavefronts per CU          6.25, 6.05, 5.7 TB/s
+//   the same with 8 (N=8) or 6 (N=16, 32) wavefronts per CU         6.25, 6.05, 5.7 TB/s
 // (one stream in place: 6.55).  More in flight only spreads the accesses to an HBM page
 // apart in time.  A wavefront that goes on to a second tile loses 10-20%: loads and stores
 // share one in-order counter, so its next loads wait behind its own stores.  Hence one
@@ -104,29 +104,40 @@ __device__ __forceinline__ _Float16 finish_one(_Float16 v, const RingArgs& a) { 
 template <typename T>
 using Global = T __attribute__((address_space(1)))*;
 
-// The same number, which the compiler cannot tell: a burst's loads and its additions test
-// it separately, and joining the two tests would copy the code for every length.
+// The same number, which the compiler cannot tell: a burst's loads and its additions test it
+// separately, and joining the two tests would copy the code for every length.
 __device__ __forceinline__ int same_count(int v) {
   asm("" : "+s"(v));
   return v;
 }
 
+// A pointer every lane has alike, read where this stands: the compiler would otherwise read
+// each behind the test of its own load, one memory round trip after the other.
+template <typename T>
+__device__ __forceinline__ T* uniform_here(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
+}
+
 // One vector per lane.  ptr(k) is the address of the stretch's first element on the k-th
-// rank of its ring (rank c+k mod N); MT is FoldTypes::vec or, unaligned, ::uvec.
+// rank of its ring (rank c+k mod N), readable, if meaningless, up to the next multiple of 16
+// past the last one; MT is FoldTypes::vec or, unaligned, ::uvec.
 template <typename TT, typename TB, int DIV, int B, typename MT, typename Ptr>
 __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a) {
   using F = FoldTypes<TT, TB>;
   using vec = typename F::vec;
   const unsigned off = threadIdx.x * 16u;  // unsigned: a scalar base and a 32-bit offset per access
   typename F::acc s = (typename F::acc)((TB)-0.0f);  // x + -0 = x for every x
-  auto at = [&](int k) { return (Global<MT>)((Global<char>)ptr(k) + off); };
+  auto at = [&](TT* p) { return (Global<MT>)((Global<char>)p + off); };
   const int n = a.n;
   int k0 = 0;
 #pragma unroll 1
   for (; k0 + B <= n; k0 += B) {  // whole bursts, no test between the loads
     vec x[B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) x[j] = __builtin_nontemporal_load(at(k0 + j));
+    for (int j = 0; j < B; ++j) x[j] = __builtin_nontemporal_load(at(ptr(k0 + j)));
     __builtin_amdgcn_sched_barrier(0);  // no addition, and so no wait, before the last load is out
 #pragma unroll
     for (int j = 0; j < B; ++j) s = F::in(x[j]) + s;
@@ -135,17 +146,20 @@ __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a) 
 #pragma unroll 1
   for (; k0 < n; k0 += R) {
     vec x[R];
+    TT* p[R];
     const int left = n - k0, adds = same_count(left);
 #pragma unroll
+    for (int j = 0; j < R; ++j) p[j] = uniform_here(ptr(k0 + j));
+#pragma unroll
     for (int j = 0; j < R; ++j)
-      if (j < left) x[j] = __builtin_nontemporal_load(at(k0 + j));
+      if (j < left) x[j] = __builtin_nontemporal_load(at(p[j]));
 #pragma unroll
     for (int j = 0; j < R; ++j)
       if (j < adds) s = F::in(x[j]) + s;
   }
   const MT o = F::out(finish_vec<DIV>(s, a));
 #pragma unroll 4
-  for (int k = 0; k < n; ++k) __builtin_nontemporal_store(o, at(k));
+  for (int k = 0; k < n; ++k) __builtin_nontemporal_store(o, at(ptr(k)));
 }
 
 // The same for one element per lane: the elements past a stretch's last whole vector.  Loads
@@ -190,8 +204,15 @@ constexpr int fold_waves(int burst) { return burst == 8 ? 4 : 2; }
 // Host side: the loads of a burst for n ranks (one instantiation each).
 inline int fold_burst(int n) { return n <= 8 ? 8 : n <= 16 ? 16 : 32; }
 
-// LDS bytes that let 8 (bursts of 8) or 6 (longer bursts) one-wavefront blocks onto a CU.
-inline unsigned fold_lds(int burst) { return (160u << 10) / (burst == 8 ? 8 : 6) / 512 * 512 - 512; }
+// LDS bytes per block that leave about 88 loads of n ranks in flight per CU and lane, 6
+// wavefronts at least: 11 for 8 ranks (265 us on ResNet-50's 102 MB per rank; 289 with 6, 286
+// with 20), 14 for 6, 6 for 16 and more (511 us on Inception-V3's 95 MB; 558 with 5, 560 with
+// 16; VGG-16 on 32 ranks 6.28 ms; 6.58 with 5, 6.37 with 8).
+inline unsigned fold_lds(int n) {
+  const int loads = n < 32 ? n : 32;
+  const int waves = 88 / loads > 6 ? 88 / loads : 6;
+  return waves >= 32 ? 0 : (160u << 10) / waves / 512 * 512 - 512;
+}
 
 }  // namespace
 }  // namespace hvdx

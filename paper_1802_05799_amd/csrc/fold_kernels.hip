@@ -1,5 +1,6 @@
-// The whole ring in one launch over flat rank buffers.  fold.hpp has the wavefront's work
-// and why it has this shape.
+// The whole ring in one launch, over flat rank buffers (fold_flat_kernel) or over the
+// tensors of a table (fold_table_kernel).  fold.hpp has the wavefront's work and why it
+// has this shape.
 
 #include "fold.hpp"
 
@@ -32,6 +33,30 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
   }
 }
 
+// ---- the tensors of a table -------------------------------------------------------------
+//
+// kFoldParts blocks per tile of the table, one per 64*V elements of it; the table lists
+// every tensor's ranks twice over, too.
+
+constexpr int64_t kFoldRow = 1 << 22;  // blocks in a row of the grid, when there are more than one row
+
+template <typename TT, typename TB, int DIV, int B>
+__global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(FoldTable t, RingArgs a) {
+  constexpr int S = kFoldLanes * FoldTypes<TT, TB>::V;
+  const int64_t b = (int64_t)blockIdx.y * kFoldRow + blockIdx.x;
+  if (b >= t.ntiles * kFoldParts) return;
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  const i32x4 w = reinterpret_cast<const i32x4*>(t.tiles)[b / kFoldParts];  // a FoldTile in one load
+  const uint32_t bits = (uint32_t)w[3];
+  const int part = (int)(b % kFoldParts) * S;
+  const int left = (int)(bits & 0xffff) - part;
+  if (left <= 0) return;
+  void* const* p = t.ptrs + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
+  const int64_t li = ((int64_t)w[1] << 32 | (uint32_t)w[0]) + part;
+  auto ptr = [&](int k) { return static_cast<TT*>(p[k]) + li; };
+  fold_stretch<TT, TB, DIV, B>(ptr, a, left < S ? left : S, bits >> 24);
+}
+
 // Blocks at or below which the wavefronts per CU are left alone: with no more than that the
 // chip is not full, and what counts is that every block is resident at once.
 constexpr int64_t kFoldFewBlocks = 256 * 16;
@@ -57,13 +82,27 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
   if (bx > (1 << 22)) bx = 1 << 22;
   const dim3 grid((unsigned)bx, (unsigned)a.n);
   const int burst = fold_burst(a.n);
-  const unsigned lds = bx * a.n <= kFoldFewBlocks ? 0 : fold_lds(burst);
+  const unsigned lds = bx * a.n <= kFoldFewBlocks ? 0 : fold_lds(a.n);
   RingPtrs ptrs;
   for (int r = 0; r < a.n; ++r) ptrs.p[r] = ptrs.p[a.n + r] = bufs.p[r];
 #define HVDX_FLAT(TT, TB, DIV, B) \
   HVDX_LAUNCH((fold_flat_kernel<TT, TB, DIV, B>), grid, dim3(kFoldLanes), lds, stream, ptrs, a, aligned)
   HVDX_FOLD_ALL(HVDX_FLAT)
 #undef HVDX_FLAT
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
+                             hipStream_t stream) {
+  const int64_t blocks = t.ntiles * kFoldParts;
+  const int64_t bx = blocks < kFoldRow ? blocks : kFoldRow;
+  const dim3 grid((unsigned)bx, (unsigned)((blocks + bx - 1) / bx));
+  const int burst = fold_burst(a.n);
+  const unsigned lds = blocks <= kFoldFewBlocks ? 0 : fold_lds(a.n);
+#define HVDX_TABLE(TT, TB, DIV, B) \
+  HVDX_LAUNCH((fold_table_kernel<TT, TB, DIV, B>), grid, dim3(kFoldLanes), lds, stream, t, a)
+  HVDX_FOLD_ALL(HVDX_TABLE)
+#undef HVDX_TABLE
   return hipGetLastError();
 }
 

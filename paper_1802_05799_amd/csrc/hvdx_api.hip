@@ -982,6 +982,120 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "tiled copy-out launch");
 }
 
+int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const int64_t* offset,
+                              const int32_t* bucket_of, const int64_t* bucket_count, int ntensors, int nbuckets,
+                              int tensor_dtype, int buf_dtype, int nranks, void* table, int64_t capacity,
+                              int64_t* ntiles) {
+  static const char* what = "hvdx_fuse_cycle_table";
+  if (ntensors < 0 || nbuckets < 0 || !ntiles ||
+      (ntensors > 0 && (!tensors || !numel || !offset || !bucket_of || !bucket_count)))
+    return fail(HVDX_ERR_INVALID, "%s: bad tensor table", what);
+  const int es = elem_size(tensor_dtype);
+  if (!es || !elem_size(buf_dtype)) return fail(HVDX_ERR_INVALID, "%s: unknown dtype", what);
+  if (tensor_dtype == HVDX_FLOAT16 && buf_dtype == HVDX_FLOAT32)
+    return fail(HVDX_ERR_UNSUPPORTED, "%s: float16 tensors with a float32 buffer", what);
+  if (nranks < 1 || nranks > HVDX_MAX_RANKS)
+    return fail(HVDX_ERR_INVALID, "%s: nranks=%d outside 1..%d", what, nranks, HVDX_MAX_RANKS);
+  if (capacity < 0 || (capacity > 0 && !table) || (reinterpret_cast<uintptr_t>(table) & 15))
+    return fail(HVDX_ERR_INVALID, "%s: bad capacity or table not 16-byte aligned", what);
+  for (int t = 0; t < ntensors; ++t) {
+    const int b = bucket_of[t];
+    if (b < 0 || b >= nbuckets) return fail(HVDX_ERR_INVALID, "%s: tensor %d in buffer %d of %d", what, t, b, nbuckets);
+    if (bucket_count[b] < 0 || bucket_count[b] > (INT64_MAX >> 4))
+      return fail(HVDX_ERR_INVALID, "%s: bad length of buffer %d", what, b);
+    if (numel[t] < 0 || offset[t] < 0 || offset[t] > bucket_count[b] || numel[t] > bucket_count[b] - offset[t])
+      return fail(HVDX_ERR_INVALID, "%s: tensor %d does not fit its buffer", what, t);
+    for (int r = 0; r < nranks && numel[t] > 0; ++r) {
+      const uintptr_t p = reinterpret_cast<uintptr_t>(tensors[(int64_t)r * ntensors + t]);
+      if (!p || p % es)
+        return fail(HVDX_ERR_INVALID, "%s: rank %d tensor %d is NULL or not aligned to its element size", what, r, t);
+    }
+  }
+  const int64_t npointers = hvdx::fold_pointers(ntensors, nranks);
+  const int64_t ptr_bytes = npointers * (int64_t)sizeof(void*);  // a multiple of 16
+  void** ptrs = static_cast<void**>(table);
+  hvdx::FoldTile* tiles = reinterpret_cast<hvdx::FoldTile*>(static_cast<char*>(table) + ptr_bytes);
+  const int64_t room = table && capacity >= ptr_bytes ? (capacity - ptr_bytes) / (int64_t)sizeof(hvdx::FoldTile) : -1;
+  const int64_t vec = hvdx::tile_vec_elems(tensor_dtype, buf_dtype);
+  const int64_t tile = hvdx::kFoldParts * 64 * vec;
+  int64_t n = 0;
+  if (!table) {  // an upper bound: a piece per chunk, its tiles, and what precedes its first 16-byte boundary
+    for (int t = 0; t < ntensors; ++t) {
+      const int64_t q = bucket_count[bucket_of[t]] / nranks;
+      const int64_t pieces = q ? std::min<int64_t>(nranks, numel[t] / q + 2) : std::min<int64_t>(nranks, numel[t]);
+      n += numel[t] / tile + 3 * pieces;
+    }
+    *ntiles = n;
+    return ptr_bytes + n * (int64_t)sizeof(hvdx::FoldTile);
+  }
+  for (int i = 0; i < hvdx::kFoldPad && room >= 0; ++i) ptrs[npointers - hvdx::kFoldPad + i] = nullptr;
+  for (int t = 0; t < ntensors; ++t) {
+    for (int r = 0; r < nranks && room >= 0; ++r)
+      ptrs[(int64_t)t * 2 * nranks + r] = ptrs[(int64_t)t * 2 * nranks + nranks + r] =
+          tensors[(int64_t)r * ntensors + t];
+    if (numel[t] == 0) continue;
+    const int64_t count = bucket_count[bucket_of[t]];
+    const int64_t q = count / nranks, rem = count % nranks, big = rem * (q + 1);
+    // Cut at chunk ends and where rank 0's addresses are multiples of a tile.  If the ranks' tensors lie
+    // alike to 16 bytes, a piece that starts off a 16-byte boundary ends at the next one, so that every
+    // other piece can be moved by aligned vectors; if not, none can.
+    const int64_t at0 = (int64_t)(reinterpret_cast<uintptr_t>(tensors[t]) / es % tile);
+    bool alike = true;
+    for (int r = 1; r < nranks; ++r)
+      alike = alike && (int64_t)(reinterpret_cast<uintptr_t>(tensors[(int64_t)r * ntensors + t]) / es % vec) == at0 % vec;
+    const int64_t p0 = offset[t], p1 = p0 + numel[t];
+    for (int64_t p = p0, c = p < big ? p / (q + 1) : rem + (p - big) / q; p < p1; ++c) {
+      const int64_t stop = std::min(p1, (c + 1) * q + std::min<int64_t>(c + 1, rem));  // of this chunk's piece
+      while (p < stop) {
+        const int64_t at = at0 + (p - p0);
+        const bool off = at & (vec - 1);
+        const int64_t len = std::min(stop - p, alike && off ? vec - (at & (vec - 1)) : tile - (at & (tile - 1)));
+        if (n < room) {
+          tiles[n].li = p - p0;
+          tiles[n].tensor = t;
+          tiles[n].bits = (uint32_t)len | (uint32_t)c << 16 | (uint32_t)(alike && !off) << 24;
+        }
+        ++n;
+        p += len;
+      }
+    }
+  }
+  *ntiles = n;
+  if (n > room)
+    return fail(HVDX_ERR_WORKSPACE, "%s: %lld tiles, room for %lld", what, (long long)n, (long long)room);
+  return ptr_bytes + n * (int64_t)sizeof(hvdx::FoldTile);
+}
+
+int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t count, int tensor_dtype, int buf_dtype,
+                    int nranks, int op, int direct, void* stream) {
+  static const char* what = "hvdx_fuse_cycle";
+  if (ntensors < 0 || ntiles < 0 || (ntiles > 0 && (!table || ntensors == 0)))
+    return fail(HVDX_ERR_INVALID, "%s: bad table", what);
+  if (reinterpret_cast<uintptr_t>(table) & 15) return fail(HVDX_ERR_INVALID, "%s: table is not 16-byte aligned", what);
+  if (!elem_size(tensor_dtype) || !elem_size(buf_dtype)) return fail(HVDX_ERR_INVALID, "%s: unknown dtype", what);
+  if (tensor_dtype == HVDX_FLOAT16 && buf_dtype == HVDX_FLOAT32)
+    return fail(HVDX_ERR_UNSUPPORTED, "%s: float16 tensors with a float32 buffer", what);
+  if (nranks < 1 || nranks > HVDX_MAX_RANKS)
+    return fail(HVDX_ERR_INVALID, "%s: nranks=%d outside 1..%d", what, nranks, HVDX_MAX_RANKS);
+  if (op != HVDX_SUM && op != HVDX_AVERAGE) return fail(HVDX_ERR_INVALID, "%s: unknown op %d", what, op);
+  if (ntiles > HVDX_CYCLE_MAX_TILES) return fail(HVDX_ERR_UNSUPPORTED, "%s: too many tiles", what);
+  if (ntiles == 0) return HVDX_OK;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const int kind = direct ? HVDX_KERNEL_RING_SMALL : HVDX_KERNEL_CYCLE_SMALL;
+  const int dtype = direct ? tensor_dtype : buf_dtype;
+  const int compress = direct && tensor_dtype != buf_dtype ? HVDX_COMPRESS_FP16 : HVDX_COMPRESS_NONE;
+  TimedLaunch timed(kind, -1, nranks, dtype, compress, count, st);
+  TimedLaunch timed_phase(kind, -1, nranks, dtype, compress, count, st, -1, true);
+  hvdx::FoldTable k;
+  k.ptrs = static_cast<void* const*>(table);
+  k.tiles = reinterpret_cast<const hvdx::FoldTile*>(static_cast<const char*>(table) +
+                                                    hvdx::fold_pointers(ntensors, nranks) * (int64_t)sizeof(void*));
+  k.ntiles = ntiles;
+  const hipError_t e = hvdx::launch_fold_table(k, ring_args(nranks, count, 0), tensor_dtype, buf_dtype,
+                                               div_mode(op, nranks), st);
+  return e == hipSuccess ? HVDX_OK : hip_fail(e, "whole-cycle launch");
+}
+
 int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const int64_t* offset, int ntensors,
                               int tensor_dtype, void* const* bufs, int64_t buf_count, int buf_dtype, int nranks,
                               int op, void* stream) {

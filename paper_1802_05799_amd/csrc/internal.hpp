@@ -145,6 +145,23 @@ hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, 
 // the messages in registers.  Over flat rank buffers (a holds their partition):
 hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
                             bool aligned, hipStream_t stream);
+// ... and over the tensors of a table, where a tile is at most kFoldParts * 64 16-byte vectors
+// of one tensor in one ring chunk.
+constexpr int kFoldParts = 4;
+struct alignas(16) FoldTile {
+  int64_t li;      // the tile's first element in its tensor
+  int32_t tensor;
+  uint32_t bits;   // elements, the ring's first rank << 16, 16-byte aligned on every rank << 24
+};
+constexpr int kFoldPad = 16;  // pointers a burst may read past the last tensor's
+constexpr int64_t fold_pointers(int64_t ntensors, int nranks) { return ntensors * 2 * nranks + kFoldPad; }
+struct FoldTable {
+  void* const* ptrs;  // DEVICE [ntensors][2 * nranks]: each tensor's ranks, twice over, then kFoldPad zeros
+  const FoldTile* tiles;  // DEVICE
+  int64_t ntiles;
+};
+hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
+                             hipStream_t stream);
 
 // Broadcast chain step (broadcast_kernels.hip).
 struct BcastArgs {

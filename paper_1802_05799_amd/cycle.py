@@ -16,15 +16,21 @@ paper's step 2 describes.  The descriptor arrays the kernels read (tensor pointe
 sizes, offsets, tile tables) are uploaded once at construction, so the tensors must
 stay allocated and in place for the object's lifetime.
 
-Buckets of at most `small_bucket_bytes` per rank (4 MiB by default) run their whole
-cycle in one launch (hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small): there a
-ring step's launch costs more than its messages.  Fused buckets on the per-step path
+By default all of that runs in one launch for every fusion buffer and one for every tensor
+reduced by itself (hvdx_fuse_cycle): each lane takes its elements through all 2(N-1)
+steps of the ring in their order, the messages in registers, so an element is read once
+and written once per rank, 2N elements moved instead of the 5N-6 of a launch per step
+(VGG-16 on 32 ranks: 12.9 ms in steps, 6.2 ms in one launch).  An argument that asks for
+the steps themselves (see FusedAllreduce) gets a launch, and a timeline record, per step;
+buckets of at most `small_bucket_bytes` per rank then still run in one launch
+(hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small).  Fused buckets on the per-step path
 run in groups, in plan order, every launch serving the whole group (up to four
 buffers with the ring on the tensors, else two), each member after the first with
 fusion buffers of its own.  Same bits either way.
 """
 from __future__ import annotations
 
+import threading
 from dataclasses import dataclass
 
 import torch
@@ -50,6 +56,15 @@ class Bucket:
     tiles: tuple | None = None  # (device copy-in table, tiles, device copy-out table, tiles)
     group: tuple = ()  # the buckets (this one included) whose cycles share every launch, or ()
     slot: int = 0  # position in the group: slot k uses fusion buffer set k; slot 0 runs the group
+
+
+@dataclass
+class _Cycle:
+    """One hvdx_fuse_cycle launch: its buckets, their device table and the call's arguments."""
+    kind: str  # "cycle_small" (fusion buffers) or "ring_small" (tensors reduced by themselves)
+    members: tuple
+    table: torch.Tensor
+    args: tuple
 
 
 def _check_disjoint(tensors) -> None:
@@ -140,8 +155,12 @@ class FusedAllreduce:
         self.tiled_flags = L.TILED_BUFFERS
         if replace_in_tensors and self.tiled:
             self.tiled_flags = L.TILED_REPLACE_IN_TENSORS | (L.TILED_ADD_FROM_TENSORS if add_from_tensors else 0)
+        # every per-step option at its default: the call is one launch for the fusion buffers and
+        # one for the direct tensors
+        whole = (self.fuse_boundary and tiled and replace_in_tensors and add_from_tensors and pair_buckets
+                 and small_bucket_bytes >= L.SMALL_BUCKET_BYTES and n >= 2)
         self.groups = []
-        if pair_buckets and self.fuse_boundary and n >= 3:
+        if pair_buckets and self.fuse_boundary and n >= 3 and not whole:
             # fused buckets on the per-step path, grouped in plan order: with the ring on the
             # tensors as many as one launch takes, else two (the two-buffer kernels); a group
             # runs at its first member's place, so a direct tensor or small bucket between its
@@ -167,25 +186,38 @@ class FusedAllreduce:
                     self.buckets[i].group, self.buckets[i].slot = members, slot
 
         dev = self.device
-        # one fusion buffer per rank, allocated once and reused for every bucket; the other
-        # members of a group run at the same time as the first and have buffers of their own
-        nslots = max([len(g) for g in self.groups], default=1)
-        caps = [max([b.count for b in self.buckets if not b.direct and b.slot == k], default=0) for k in range(nslots)]
-        self.buf_sets = [[torch.empty(max(c, 1) if k == 0 else c, dtype=_TORCH_DTYPE[self.buf_dtype], device=dev)
-                          for _ in range(n)] for k, c in enumerate(caps)]
-        self.bufs = self.buf_sets[0]
-        ws = max([L.hvdx_ring_workspace_bytes(n, b.count, self.dtype, self.compress)
-                  for b in self.buckets if b.direct], default=0)
-        self.workspace = torch.empty(max(ws, 1), dtype=torch.uint8, device=dev)
-        self.workspace_bytes = ws
+        self.workspace_bytes = max([L.hvdx_ring_workspace_bytes(n, b.count, self.dtype, self.compress)
+                                    for b in self.buckets if b.direct], default=0)
+        self._scratch = None
+        self._scratch_lock = threading.Lock()
+        if not whole:
+            self._buffers()
+        ptrs = [[x.data_ptr() for x in ts] for ts in self.tensors]
         for b in self.buckets:
             if b.direct:
                 continue
-            b.numel_dev = torch.tensor([self.numel[t] for t in b.tensors], dtype=torch.int64, device=dev)
-            b.offset_dev = torch.tensor(b.offsets, dtype=torch.int64, device=dev)
-            b.ptrs_dev = torch.tensor([self.tensors[r][t].data_ptr() for r in range(n) for t in b.tensors],
-                                      dtype=torch.int64, device=dev)
-        if self.tiled:
+            k = len(b.tensors)
+            b.numel_dev, b.offset_dev, b.ptrs_dev = torch.tensor(
+                [self.numel[t] for t in b.tensors] + b.offsets + [p[t] for p in ptrs for t in b.tensors],
+                dtype=torch.int64, device=dev).split([k, k, n * k])
+        self._cycles = None
+        if whole:
+            self._cycles = []
+            for direct, kind in ((False, "cycle_small"), (True, "ring_small")):
+                members = [i for i, b in enumerate(self.buckets) if b.direct == direct and b.count > 0]
+                if not members:
+                    continue
+                bs = [self.buckets[i] for i in members]
+                ids = [t for b in bs for t in b.tensors]
+                table, ntiles = L.hvdx_fuse_cycle_table(
+                    [p[t] for p in ptrs for t in ids], [self.numel[t] for t in ids], [o for b in bs for o in b.offsets],
+                    [k for k, b in enumerate(bs) for _ in b.tensors], [b.count for b in bs], self.dtype, self.buf_dtype, n)
+                dev_table = torch.frombuffer(table, dtype=torch.uint8).to(dev)
+                self._cycles.append(_Cycle(kind, tuple(members), dev_table, (
+                    dev_table.data_ptr(), len(ids), ntiles, sum(b.count for b in bs), self.dtype, self.buf_dtype, n,
+                    self.op, direct)))
+            self._cycles.sort(key=lambda c: c.members[0])  # in plan order
+        elif self.tiled:
             for b in self.buckets:
                 if b.direct or b.small or b.count == 0:
                     continue
@@ -196,8 +228,39 @@ class FusedAllreduce:
                     host = torch.frombuffer(bytearray(bytes(arr)), dtype=torch.uint8)
                     tabs += [host.to(dev), k]
                 b.tiles = tuple(tabs)
-        self._buf_ptrs = [[x.data_ptr() for x in bs] for bs in self.buf_sets]
         _timeline.start_from_env()
+
+    # ---- memory of the per-step path: allocated with the object, or, where calls do not need it, when
+    # one of the steps below is first asked for ----------------------------------------------------
+    def _buffers(self):
+        with self._scratch_lock:
+            if self._scratch is None:
+                # one fusion buffer per rank, allocated once and reused for every bucket; the other
+                # members of a group run at the same time as the first and have buffers of their own
+                nslots = max([len(g) for g in self.groups], default=1)
+                caps = [max([b.count for b in self.buckets if not b.direct and b.slot == k], default=0)
+                        for k in range(nslots)]
+                sets = [[torch.empty(max(c, 1) if k == 0 else c, dtype=_TORCH_DTYPE[self.buf_dtype],
+                                     device=self.device) for _ in range(self.nranks)] for k, c in enumerate(caps)]
+                workspace = torch.empty(max(self.workspace_bytes, 1), dtype=torch.uint8, device=self.device)
+                self._scratch = (sets, workspace, [[x.data_ptr() for x in bs] for bs in sets])
+            return self._scratch
+
+    @property
+    def buf_sets(self):
+        return self._buffers()[0]
+
+    @property
+    def bufs(self):
+        return self.buf_sets[0]
+
+    @property
+    def workspace(self):
+        return self._buffers()[1]
+
+    @property
+    def _buf_ptrs(self):
+        return self._buffers()[2]
 
     # ---- the steps, exposed separately for tracing ------------------------------------
     def pack(self, b: Bucket, stream: int) -> None:
@@ -238,7 +301,7 @@ class FusedAllreduce:
     def fused_cycle(self, b: Bucket, stream: int) -> None:
         """A fusion buffer's copy-in, ring and copy-out with the boundary steps fused
         (or, for a small bucket, all in one launch)."""
-        if self.tiled and not b.small:
+        if b.tiles is not None:
             L.hvdx_fuse_allreduce_tiled([self.tiled_desc(b)], self.dtype, self.buf_dtype, self.nranks, self.op,
                                         self.tiled_flags, stream)
             return
@@ -271,6 +334,8 @@ class FusedAllreduce:
         (the one-rank compressed round trip),
         "cycle_small" or "ring_small" (a small bucket's whole cycle in one launch).
         A launch that serves a group of buckets names them all: (kind, (i, j, ...), step)."""
+        if self._cycles is not None:
+            return [(c.kind, c.members if len(c.members) > 1 else c.members[0], -1) for c in self._cycles]
         out = []
         n = self.nranks
         for bi, b in enumerate(self.buckets):
@@ -339,6 +404,10 @@ class FusedAllreduce:
     def __call__(self, stream: int | None = None) -> None:
         if stream is None:
             stream = torch.cuda.current_stream(self.device).cuda_stream
+        if self._cycles is not None:
+            for c in self._cycles:
+                L.hvdx_fuse_cycle(*c.args, stream)
+            return
         for i, b in enumerate(self.buckets):
             if b.group and b.slot == 0:
                 self.fused_group(b.group, stream)

@@ -8,6 +8,7 @@ import torch
 
 import paper_1802_05799_amd as hv
 from _gpu import NP_TO_HV, OPS, assert_bits_equal, from_gpu_rows, say, to_gpu_rows
+from oracle import allreduce
 from test_gpu_ring import inputs, oracle_ring
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,80 @@ def test_flat_buffers_compressed(n):
             hv.hvdx_fold_allreduce([r.data_ptr() for r in rows], n, count, hv.FLOAT32, hv.AVERAGE, hv.COMPRESS_FP16,
                                    torch.cuda.current_stream().cuda_stream)
             assert_bits_equal(from_gpu_rows(rows), want, f"n={n} count={count}")
+
+
+def rank_lists(rng, n, numel, dtype, layout):
+    """Host and device tensor lists; "packed": views end to end; "unalike": each rank's tensors
+    at their own distance from a 16-byte boundary."""
+    host = [[(rng.standard_normal(k) * 0.01).astype(dtype) for k in numel] for _ in range(n)]
+    dev = []
+    for r, row in enumerate(host):
+        gap = r % 5 if layout == "unalike" else 0
+        flat = torch.full((sum(numel) + gap * (len(numel) + 1) + 8,), 7.0, dtype=torch.from_numpy(row[0]).dtype,
+                          device="cuda")
+        at, ts = 0, []
+        for x in row:
+            at += gap
+            ts.append(flat[at : at + x.size])
+            ts[-1].copy_(torch.from_numpy(x))
+            at += x.size
+        dev.append(ts)
+    return host, dev
+
+
+LIST_CASES = [
+    # (numel, ranks, threshold bytes, binary16 tensors, compress)
+    ([1, 2, 3, 1023, 1024, 1025, 4099, 70001], 2, 64 << 20, False, False),
+    ([255, 256, 257, 5, 30000, 0, 9], 7, 40000, False, False),  # fused and direct
+    ([255, 256, 257, 5, 30000, 0, 9], 8, 0, False, False),  # every tensor by itself
+    ([513, 64, 64, 64, 40007], 16, 64 << 20, True, False),  # binary16 tensors
+    ([513, 64, 64, 64, 40007], 33, 50000, False, True),  # compressed, fused and direct
+    ([3, 900, 20001], 128, 30000, False, True),
+    ([2000, 1, 3001], 24, 4096, True, False),
+]
+
+
+@pytest.mark.parametrize("layout", ["packed", "unalike"])
+@pytest.mark.parametrize("case", range(len(LIST_CASES)))
+def test_default_cycle_in_one_launch(case, layout):
+    numel, n, threshold, half, compress = LIST_CASES[case]
+    rng = np.random.default_rng(5200 + case)
+    for op in ("average", "sum"):
+        say(f"one-launch cycle case {case} {layout} {op}")
+        host, dev = rank_lists(rng, n, numel, np.float16 if half else np.float32, layout)
+        want = allreduce.allreduce(host, op, compress=compress, threshold=threshold)
+        ar = hv.FusedAllreduce(dev, op=op, compress=compress, threshold_bytes=threshold)
+        assert {k for k, _, _ in ar.kernel_sequence()} <= {"cycle_small", "ring_small"}
+        ar()
+        torch.cuda.synchronize()
+        for r in range(n):
+            for t in range(len(numel)):
+                assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
+
+
+def test_steps_of_a_one_launch_object():
+    """The pieces a one-launch object offers for tracing still run: per bucket the copies and the
+    ring's halves, or the whole cycle, on buffers allocated when first asked for."""
+    numel, n, threshold = [3000, 5, 257, 90000], 5, 40000
+    rng = np.random.default_rng(5300)
+    for compress in (False, True):
+        for whole in (False, True):
+            say(f"pieces of a one-launch object compress={compress} whole={whole}")
+            host, dev = rank_lists(rng, n, numel, np.float32, "packed")
+            ar = hv.FusedAllreduce(dev, compress=compress, threshold_bytes=threshold)
+            s = torch.cuda.current_stream().cuda_stream
+            for b in ar.buckets:
+                if whole and not b.direct:
+                    ar.fused_cycle(b, s)
+                    continue
+                if not b.direct:
+                    ar.pack(b, s)
+                ar.ring_phase(b, hv.PHASE_REDUCE_SCATTER, s)
+                ar.ring_phase(b, hv.PHASE_ALLGATHER, s)
+                if not b.direct:
+                    ar.unpack(b, s)
+            torch.cuda.synchronize()
+            want = allreduce.allreduce(host, "average", compress=compress, threshold=threshold)
+            for r in range(n):
+                for t in range(len(numel)):
+                    assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
