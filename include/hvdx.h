@@ -340,7 +340,7 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
  *   table      DEVICE copy of the table, 16-byte aligned (not checked: other contents make
  *              the kernel read or write outside the tensors)
  *   ntiles     <= HVDX_CYCLE_MAX_TILES
- *   count      the buffers' elements, for the timeline's record
+ *   count      the buffers' elements, for the launch's shape and the timeline's record
  *   direct     1 when every buffer is a tensor reduced by itself: the timeline then says so
  * Errors: HVDX_ERR_INVALID, HVDX_ERR_UNSUPPORTED (binary16 tensors with a binary32 buffer, too
  * many tiles), HVDX_ERR_HIP.

@@ -18,6 +18,8 @@
 // stores, and the end; an LDS reservation no one uses holds the wavefronts per CU down.
 #pragma once
 
+#include <algorithm>
+
 #include "ring_math.hpp"
 
 namespace hvdx {
@@ -72,32 +74,24 @@ struct FoldTypes<float, _Float16> {
   }
 };
 
-// The AVERAGE divide of a finished sum.
-template <int DIV>
-__device__ __forceinline__ f32x4 finish_vec(f32x4 s, const RingArgs& a) {
+// The AVERAGE divide of a finished sum (mode: one DivMode for the whole launch).
+__device__ __forceinline__ float finish_one(float s, const RingArgs& a, int mode) {
+  return mode == DIV_NONE ? s : mode == DIV_POW2 ? finish<DIV_POW2>(s, a) : finish<DIV_TRUE>(s, a);
+}
+__device__ __forceinline__ _Float16 finish_one(_Float16 s, const RingArgs& a, int mode) {
+  return mode == DIV_NONE ? s : mode == DIV_POW2 ? finish16<DIV_POW2>(s, a) : finish16<DIV_TRUE>(s, a);
+}
+template <int V, typename A>
+__device__ __forceinline__ A finish_vec(A s, const RingArgs& a, int mode) {
+  if (mode == DIV_POW2) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) s[k] = finish<DIV>(s[k], a);
+    for (int k = 0; k < V; ++k) s[k] = finish_one(s[k], a, DIV_POW2);
+  } else if (mode == DIV_TRUE) {
+#pragma unroll
+    for (int k = 0; k < V; ++k) s[k] = finish_one(s[k], a, DIV_TRUE);
+  }
   return s;
 }
-template <int DIV>
-__device__ __forceinline__ f16x8 finish_vec(f16x8 s, const RingArgs& a) {
-  if constexpr (DIV == DIV_POW2) return s * (f16x8)((_Float16)a.inv);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s[k] = finish16<DIV>(s[k], a);
-  return s;
-}
-template <int DIV>
-__device__ __forceinline__ f16x4 finish_vec(f16x4 s, const RingArgs& a) {
-  if constexpr (DIV == DIV_POW2) return s * (f16x4)((_Float16)a.inv);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) s[k] = finish16<DIV>(s[k], a);
-  return s;
-}
-
-template <int DIV>
-__device__ __forceinline__ float finish_one(float v, const RingArgs& a) { return finish<DIV>(v, a); }
-template <int DIV>
-__device__ __forceinline__ _Float16 finish_one(_Float16 v, const RingArgs& a) { return finish16<DIV>(v, a); }
 
 // An address known to be global memory: pointers out of a table would otherwise be accessed
 // by flat instructions, which cannot be waited for one after the other.
@@ -124,8 +118,8 @@ __device__ __forceinline__ T* uniform_here(T* p) {
 // One vector per lane.  ptr(k) is the address of the stretch's first element on the k-th
 // rank of its ring (rank c+k mod N), readable, if meaningless, up to the next multiple of 16
 // past the last one; MT is FoldTypes::vec or, unaligned, ::uvec.
-template <typename TT, typename TB, int DIV, int B, typename MT, typename Ptr>
-__device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a) {
+template <typename TT, typename TB, int B, typename MT, typename Ptr>
+__device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, int mode) {
   using F = FoldTypes<TT, TB>;
   using vec = typename F::vec;
   const unsigned off = threadIdx.x * 16u;  // unsigned: a scalar base and a 32-bit offset per access
@@ -157,15 +151,15 @@ __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a) 
     for (int j = 0; j < R; ++j)
       if (j < adds) s = F::in(x[j]) + s;
   }
-  const MT o = F::out(finish_vec<DIV>(s, a));
+  const MT o = F::out(finish_vec<F::V>(s, a, mode));
 #pragma unroll 4
   for (int k = 0; k < n; ++k) __builtin_nontemporal_store(o, at(ptr(k)));
 }
 
 // The same for one element per lane: the elements past a stretch's last whole vector.  Loads
 // past the last rank repeat its own.
-template <typename TT, typename TB, int DIV, typename Ptr>
-__device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, int e) {
+template <typename TT, typename TB, typename Ptr>
+__device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, int mode, int e) {
   constexpr int B = 8;
   const int n = a.n;
   TB s = (TB)-0.0f;
@@ -180,38 +174,51 @@ __device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, 
       s = k0 + j < n ? sum : s;
     }
   }
-  const TT o = (TT)finish_one<DIV>(s, a);
+  const TT o = (TT)finish_one(s, a, mode);
 #pragma unroll 1
   for (int k = 0; k < n; ++k) ((Global<TT>)ptr(k))[e] = o;
 }
 
 // A wavefront's stretch of m (1 .. 64*V) elements.
-template <typename TT, typename TB, int DIV, int B, typename Ptr>
-__device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int m, bool aligned) {
+template <typename TT, typename TB, int B, typename Ptr>
+__device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int mode, int m, bool aligned) {
   using F = FoldTypes<TT, TB>;
   const int lane = threadIdx.x;
   const int vecs = m / F::V, rest = m - vecs * F::V;
   if (lane < vecs) {
-    if (aligned) fold_vectors<TT, TB, DIV, B, typename F::vec>(ptr, a);
-    else fold_vectors<TT, TB, DIV, B, typename F::uvec>(ptr, a);
+    if (aligned) fold_vectors<TT, TB, B, typename F::vec>(ptr, a, mode);
+    else fold_vectors<TT, TB, B, typename F::uvec>(ptr, a, mode);
   }
-  if (lane < rest) fold_element<TT, TB, DIV>(ptr, a, vecs * F::V + lane);
+  if (lane < rest) fold_element<TT, TB>(ptr, a, mode, vecs * F::V + lane);
 }
 
 // Wavefronts per SIMD that the registers of a burst have to leave room for.
-constexpr int fold_waves(int burst) { return burst == 8 ? 4 : 2; }
+constexpr int fold_waves(int burst) { return burst <= 8 ? 4 : burst <= 16 ? 3 : 2; }
 
-// Host side: the loads of a burst for n ranks (one instantiation each).
-inline int fold_burst(int n) { return n <= 8 ? 8 : n <= 16 ? 16 : 32; }
+// Host side: the loads of a burst for n ranks (one instantiation each).  Every burst should be a
+// whole one: a shorter last one tests before each load.  TB/s, Inception-V3's tensors:
+//   9 ranks   in a burst of up to 16 5.76, of 9 6.12       24   16 + 8 5.44, 2 x 12 5.65
+//   12        in one of up to 16     5.77, of 12 6.03      40   16 + 16 + 8 5.24, 4 x 10 5.50
+//   17        16 + 1                 5.32, 9 + 8 5.62      64   4 x 16 5.41, 2 x 32 5.45
+// So: all ranks up to 16, 32 where it divides n, else the longest of 16 to 8 that divides n,
+// else near-equal ones.
+inline int fold_burst(int n) {
+  if (n <= 16) return n < 2 ? 2 : n;
+  if (n % 32 == 0) return 32;
+  for (int b = 16; b >= 8; --b)
+    if (n % b == 0) return b;
+  const int bursts = (n + 15) / 16;
+  return (n + bursts - 1) / bursts;
+}
 
-// LDS bytes per block that leave about 88 loads of n ranks in flight per CU and lane, 6
-// wavefronts at least: 11 for 8 ranks (265 us on ResNet-50's 102 MB per rank; 289 with 6, 286
-// with 20), 14 for 6, 6 for 16 and more (511 us on Inception-V3's 95 MB; 558 with 5, 560 with
-// 16; VGG-16 on 32 ranks 6.28 ms; 6.58 with 5, 6.37 with 8).
-inline unsigned fold_lds(int n) {
-  const int loads = n < 32 ? n : 32;
-  const int waves = 88 / loads > 6 ? 88 / loads : 6;
-  return waves >= 32 ? 0 : (160u << 10) / waves / 512 * 512 - 512;
+// LDS bytes per block that hold the wavefronts per CU down to what streams best with `burst`
+// loads in flight in each: 17 for 4 (6.19 TB/s; 6.0 with 12, 6.11 with 32), 12 for 6 (6.22; 6.04
+// with 10, 5.88 with 20), 10 for 8 (6.13; 6.0 with 14, 5.88 with 32), 8 for 12, 6 for 16 and 32
+// (VGG-16 on 32 ranks 6.28 ms; 6.58 with 5, 6.37 with 8).
+inline unsigned fold_lds(int burst) {
+  if (burst < 4) return 0;
+  const int waves = std::max(6, 3 + (54 + burst / 2) / burst);
+  return (160u << 10) / waves / 512 * 512 - 512;
 }
 
 }  // namespace

@@ -2,6 +2,8 @@
 // tensors of a table (fold_table_kernel).  fold.hpp has the wavefront's work and why it
 // has this shape.
 
+#include <type_traits>
+
 #include "fold.hpp"
 
 namespace hvdx {
@@ -18,8 +20,8 @@ struct RingPtrs {
   void* p[2 * HVDX_MAX_RANKS];
 };
 
-template <typename TT, typename TB, int DIV, int B>
-__global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(RingPtrs bufs, RingArgs a, bool aligned) {
+template <typename TT, typename TB, int B>
+__global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(RingPtrs bufs, RingArgs a, int mode, bool aligned) {
   constexpr int64_t S = kFoldLanes * FoldTypes<TT, TB>::V;
   const int c = blockIdx.y;
   const Chunk ch = chunk_of(c, a);
@@ -29,7 +31,7 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
     const int64_t e1 = (g + 1) * S < end ? (g + 1) * S : end;
     auto ptr = [&](int k) { return static_cast<TT*>(bufs.p[c + k]) + e0; };
     const bool al = aligned && e0 % FoldTypes<TT, TB>::V == 0;
-    fold_stretch<TT, TB, DIV, B>(ptr, a, (int)(e1 - e0), al);
+    fold_stretch<TT, TB, B>(ptr, a, mode, (int)(e1 - e0), al);
   }
 }
 
@@ -40,8 +42,8 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
 
 constexpr int64_t kFoldRow = 1 << 22;  // blocks in a row of the grid, when there are more than one row
 
-template <typename TT, typename TB, int DIV, int B>
-__global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(FoldTable t, RingArgs a) {
+template <typename TT, typename TB, int B>
+__global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(FoldTable t, RingArgs a, int mode) {
   constexpr int S = kFoldLanes * FoldTypes<TT, TB>::V;
   const int64_t b = (int64_t)blockIdx.y * kFoldRow + blockIdx.x;
   if (b >= t.ntiles * kFoldParts) return;
@@ -54,23 +56,39 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(F
   void* const* p = t.ptrs + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
   const int64_t li = ((int64_t)w[1] << 32 | (uint32_t)w[0]) + part;
   auto ptr = [&](int k) { return static_cast<TT*>(p[k]) + li; };
-  fold_stretch<TT, TB, DIV, B>(ptr, a, left < S ? left : S, bits >> 24);
+  fold_stretch<TT, TB, B>(ptr, a, mode, left < S ? left : S, bits >> 24);
 }
 
-// Blocks at or below which the wavefronts per CU are left alone: with no more than that the
-// chip is not full, and what counts is that every block is resident at once.
-constexpr int64_t kFoldFewBlocks = 256 * 16;
+// Whether to hold the wavefronts per CU down (fold_lds).  Not where all ranks' elements about fit
+// the 256 MiB Infinity Cache: then a launch is over before HBM pages are what counts, and more
+// wavefronts start faster (6 ranks of 5M binary32 elements 5.58 TB/s held, 5.83 not; of 10M 5.96 and
+// 6.15; of 20M 6.12 and 6.14; 16 ranks of 3M 5.30 and 5.50, of 10M 5.98 and 5.89).  And not where
+// more than 1/8 of the blocks have little or nothing to move (short tensors, each cut into N
+// chunks: Inception-V3's tensors reduced one by one on 16 ranks 605 us held, 580 not).
+bool fold_holds(int64_t blocks, int64_t count, int nranks, int tensor_dtype) {
+  const int64_t bytes = count * (tensor_dtype == HVDX_FLOAT16 ? 2 : 4);
+  const int64_t filled = bytes / (kFoldLanes * 16);
+  return bytes > (384ll << 20) / nranks && blocks <= filled + filled / 8;
+}
 
-#define HVDX_FOLD_BURST(F, TT, TB, DIV) \
-  if (burst == 8) F(TT, TB, DIV, 8); else if (burst == 16) F(TT, TB, DIV, 16); else F(TT, TB, DIV, 32)
-#define HVDX_FOLD_DIV(F, TT, TB) \
-  if (divmode == DIV_NONE) { HVDX_FOLD_BURST(F, TT, TB, DIV_NONE); } \
-  else if (divmode == DIV_POW2) { HVDX_FOLD_BURST(F, TT, TB, DIV_POW2); } \
-  else { HVDX_FOLD_BURST(F, TT, TB, DIV_TRUE); }
-#define HVDX_FOLD_ALL(F) \
-  if (tensor_dtype == HVDX_FLOAT16) { HVDX_FOLD_DIV(F, _Float16, _Float16) } \
-  else if (buf_dtype == HVDX_FLOAT16) { HVDX_FOLD_DIV(F, float, _Float16) } \
-  else { HVDX_FOLD_DIV(F, float, float) }
+// Calls f(TT{}, TB{}, integral_constant<burst>) for the launch's types and burst.
+template <typename TT, typename TB, typename F>
+void with_burst(int burst, const F& f) {
+  switch (burst) {
+#define HVDX_BURST(B) \
+  case B: return f(TT{}, TB{}, std::integral_constant<int, B>{});
+    HVDX_BURST(2) HVDX_BURST(3) HVDX_BURST(4) HVDX_BURST(5) HVDX_BURST(6) HVDX_BURST(7) HVDX_BURST(8) HVDX_BURST(9)
+    HVDX_BURST(10) HVDX_BURST(11) HVDX_BURST(12) HVDX_BURST(13) HVDX_BURST(14) HVDX_BURST(15) HVDX_BURST(16)
+#undef HVDX_BURST
+    default: return f(TT{}, TB{}, std::integral_constant<int, 32>{});
+  }
+}
+template <typename F>
+void with_types(int tensor_dtype, int buf_dtype, int burst, const F& f) {
+  if (tensor_dtype == HVDX_FLOAT16) with_burst<_Float16, _Float16>(burst, f);
+  else if (buf_dtype == HVDX_FLOAT16) with_burst<float, _Float16>(burst, f);
+  else with_burst<float, float>(burst, f);
+}
 
 }  // namespace
 
@@ -82,27 +100,27 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
   if (bx > (1 << 22)) bx = 1 << 22;
   const dim3 grid((unsigned)bx, (unsigned)a.n);
   const int burst = fold_burst(a.n);
-  const unsigned lds = bx * a.n <= kFoldFewBlocks ? 0 : fold_lds(a.n);
+  const unsigned lds = fold_holds(bx * a.n, a.q * a.n + a.rem, a.n, tensor_dtype) ? fold_lds(burst) : 0;
   RingPtrs ptrs;
   for (int r = 0; r < a.n; ++r) ptrs.p[r] = ptrs.p[a.n + r] = bufs.p[r];
-#define HVDX_FLAT(TT, TB, DIV, B) \
-  HVDX_LAUNCH((fold_flat_kernel<TT, TB, DIV, B>), grid, dim3(kFoldLanes), lds, stream, ptrs, a, aligned)
-  HVDX_FOLD_ALL(HVDX_FLAT)
-#undef HVDX_FLAT
+  with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
+    HVDX_LAUNCH((fold_flat_kernel<decltype(tt), decltype(tb), b.value>), grid, dim3(kFoldLanes), lds, stream, ptrs, a,
+                divmode, aligned);
+  });
   return hipGetLastError();
 }
 
-hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
-                             hipStream_t stream) {
+hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int64_t count, int tensor_dtype, int buf_dtype,
+                             int divmode, hipStream_t stream) {
   const int64_t blocks = t.ntiles * kFoldParts;
   const int64_t bx = blocks < kFoldRow ? blocks : kFoldRow;
   const dim3 grid((unsigned)bx, (unsigned)((blocks + bx - 1) / bx));
   const int burst = fold_burst(a.n);
-  const unsigned lds = blocks <= kFoldFewBlocks ? 0 : fold_lds(a.n);
-#define HVDX_TABLE(TT, TB, DIV, B) \
-  HVDX_LAUNCH((fold_table_kernel<TT, TB, DIV, B>), grid, dim3(kFoldLanes), lds, stream, t, a)
-  HVDX_FOLD_ALL(HVDX_TABLE)
-#undef HVDX_TABLE
+  const unsigned lds = fold_holds(blocks, count, a.n, tensor_dtype) ? fold_lds(burst) : 0;
+  with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
+    HVDX_LAUNCH((fold_table_kernel<decltype(tt), decltype(tb), b.value>), grid, dim3(kFoldLanes), lds, stream, t, a,
+                divmode);
+  });
   return hipGetLastError();
 }
 

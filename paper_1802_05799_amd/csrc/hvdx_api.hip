@@ -1091,7 +1091,7 @@ int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t cou
   k.tiles = reinterpret_cast<const hvdx::FoldTile*>(static_cast<const char*>(table) +
                                                     hvdx::fold_pointers(ntensors, nranks) * (int64_t)sizeof(void*));
   k.ntiles = ntiles;
-  const hipError_t e = hvdx::launch_fold_table(k, ring_args(nranks, count, 0), tensor_dtype, buf_dtype,
+  const hipError_t e = hvdx::launch_fold_table(k, ring_args(nranks, count, 0), count, tensor_dtype, buf_dtype,
                                                div_mode(op, nranks), st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "whole-cycle launch");
 }

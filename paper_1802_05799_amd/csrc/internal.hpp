@@ -160,8 +160,8 @@ struct FoldTable {
   const FoldTile* tiles;  // DEVICE
   int64_t ntiles;
 };
-hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
-                             hipStream_t stream);
+hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int64_t count, int tensor_dtype, int buf_dtype,
+                             int divmode, hipStream_t stream);  // count: elements the tiles hold, about
 
 // Broadcast chain step (broadcast_kernels.hip).
 struct BcastArgs {
