@@ -489,13 +489,14 @@ int hvdx_ring_step(void* const* bufs, int nranks, int64_t count, int dtype, int 
  * chunks of whole 16-byte units (the first (units mod N) chunks one unit longer;
  * the last unit may be short), and in step s rank root+k forwards chunk s-k to rank
  * root+k+1 (k = 0..N-2, when 0 <= s-k < N): 2N-2 steps.  Bytes are copied, not
- * interpreted, so any element type works.
+ * interpreted, so any element type works.  hvdx_broadcast runs them all in one launch,
+ * each byte from the root along the whole chain in a register; hvdx_broadcast_step runs
+ * step `step` (0 <= step < 2*nranks-2) alone.
  *
  *   bufs[nranks]  host array of device pointers, each nbytes long, pairwise
  *                 non-overlapping (16-byte alignment of all of them enables the
- *                 vector path)
+ *                 steps' vector path)
  *   nbytes        >= 0 (0 is a no-op); root in 0..nranks-1
- * hvdx_broadcast_step runs step `step` (0 <= step < 2*nranks-2) alone.
  * Errors: HVDX_ERR_INVALID, HVDX_ERR_ALIAS, HVDX_ERR_HIP.
  */
 int hvdx_broadcast(void* const* bufs, int nranks, int64_t nbytes, int root, void* stream);
@@ -503,8 +504,8 @@ int hvdx_broadcast_step(void* const* bufs, int nranks, int64_t nbytes, int root,
 
 /*
  * hvdx_broadcast_tensors -- hvdx_broadcast for many tensors in one call (paper
- * sections 4 and 5: every variable broadcast from the root at start-up), 2N-2 launches
- * in all instead of 2N-2 per tensor.  The tensors are laid end to end in a virtual
+ * sections 4 and 5: every variable broadcast from the root at start-up), one launch in
+ * all.  The tensors are laid end to end in a virtual
  * byte space, tensor t at [voffset[t], voffset[t] + nbytes[t]), and the chain of
  * hvdx_broadcast runs over that space as over one buffer of total_bytes bytes: chunk j
  * is the j-th run of whole 16-byte units, and in step s rank root+k forwards chunk s-k
@@ -517,7 +518,10 @@ int hvdx_broadcast_step(void* const* bufs, int nranks, int64_t nbytes, int root,
  *                          copies move as vectors, others byte by byte
  *   nbytes[ntensors]       DEVICE array, bytes of each tensor (>= 0)
  *   voffset[ntensors]      DEVICE array, ascending multiples of 16 with
- *                          voffset[t] >= voffset[t-1] + nbytes[t-1]
+ *                          voffset[t] >= voffset[t-1] + nbytes[t-1].  (The one launch, not the
+ *                          steps, takes any ascending starts that leave no 16-byte unit to two
+ *                          tensors, and is fastest where they lie in a 4 KiB page as the ranks'
+ *                          tensors do.)
  *   total_bytes            >= voffset[T-1] + nbytes[T-1]; 0 (or ntensors 0) is a no-op
  *   root                   0..nranks-1
  * hvdx_broadcast_layout (host) computes the densest layout: each tensor at the first

@@ -83,8 +83,8 @@ _NBYTES = operator.attrgetter("nbytes")
 class TensorBroadcast:
     """Rank `root`'s tensors copied into every other rank's (paper sections 4 and 5:
     consistent initial variables), every tensor of the list in one chain:
-    hvdx_broadcast_tensors runs the 2N-2 chain steps once for the whole list, over the
-    tensors laid end to end at 16-byte aligned starts.  Bytes are copied, not
+    hvdx_broadcast_tensors runs the chain once for the whole list, in one launch; step()
+    runs one of its 2N-2 steps, over the tensors laid end to end at 16-byte aligned starts.  Bytes are copied, not
     interpreted: tensor t must have the same byte count on every rank (any dtype), be
     contiguous, on one GPU, and share memory with no other tensor.  The descriptor
     tables are uploaded once (asynchronously, from pinned memory); the tensors must stay
@@ -120,8 +120,17 @@ class TensorBroadcast:
             raise ValueError("tensors overlap in memory")
         self.device = flat[0].device if flat else torch.device("cuda", torch.cuda.current_device())
         voff, self.total = hvdx_broadcast_layout(nbytes[0].tolist() if nt else [])
-        # one upload: the rank-major pointer table, then the byte counts, then the starts
-        host = torch.from_numpy(np.concatenate([ptr, nbytes[0], np.asarray(voff, dtype=np.int64), [0]]))
+        # The whole call is one launch, whose wavefronts take stretches of the virtual space: its own
+        # layout starts each tensor where rank 0's address lies in a 4 KiB page, so that the
+        # stretches end with the tensors' cache lines
+        starts0, at = [], 0
+        for p, k in zip(ptr[:nt].tolist(), nbytes[0].tolist()):
+            at = -(-at // 16) * 16
+            at += (p - at) % 4096
+            starts0.append(at)
+            at += k
+        # one upload: the rank-major pointer table, then the byte counts, then both layouts' starts
+        host = torch.from_numpy(np.concatenate([ptr, nbytes[0], np.asarray(voff + starts0, dtype=np.int64), [0]]))
         self.tables = host.pin_memory().to(self.device, non_blocking=True)
         upload = torch.cuda.current_stream(self.device)
         self._ready = torch.cuda.Event()  # a call on another stream waits for the upload
@@ -130,6 +139,7 @@ class TensorBroadcast:
         k = n * nt
         self._args = (self.tables.data_ptr(), self.tables.data_ptr() + 8 * k, self.tables.data_ptr() + 8 * (k + nt),
                       nt, self.total, n)
+        self._call_args = (*self._args[:2], self._args[2] + 8 * nt, nt, at, n)
         self.tensors = per_rank  # keeps the tensors alive as long as the tables point at them
 
     def _stream(self, stream):
@@ -141,7 +151,7 @@ class TensorBroadcast:
         return stream
 
     def __call__(self, root: int = 0, stream: int | None = None) -> None:
-        hvdx_broadcast_tensors(*self._args, root, self._stream(stream))
+        hvdx_broadcast_tensors(*self._call_args, root, self._stream(stream))
 
     def step(self, root: int, step: int, stream: int | None = None) -> None:
         """One chain step alone (hvdx_broadcast_tensors_step)."""

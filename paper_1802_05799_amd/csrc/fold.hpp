@@ -93,11 +93,6 @@ __device__ __forceinline__ A finish_vec(A s, const RingArgs& a, int mode) {
   return s;
 }
 
-// An address known to be global memory: pointers out of a table would otherwise be accessed
-// by flat instructions, which cannot be waited for one after the other.
-template <typename T>
-using Global = T __attribute__((address_space(1)))*;
-
 // The same number, which the compiler cannot tell: a burst's loads and its additions test it
 // separately, and joining the two tests would copy the code for every length.
 __device__ __forceinline__ int same_count(int v) {

@@ -1179,6 +1179,7 @@ static int check_bcast(void* const* bufs, int nranks, int64_t nbytes, int root, 
   return HVDX_OK;
 }
 
+// Chain step `step`, or, for step < 0, the whole broadcast in one launch.
 static int bcast_step(void* const* bufs, int nranks, int64_t nbytes, int root, int step, hipStream_t st) {
   hvdx::BcastArgs a{};
   a.n = nranks;
@@ -1192,7 +1193,8 @@ static int bcast_step(void* const* bufs, int nranks, int64_t nbytes, int root, i
   for (int r = 0; r < nranks; ++r) vok = vok && aligned16(bufs[r]);
   TimedLaunch timed(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, nbytes, st, root);
   TimedLaunch timed_phase(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, nbytes, st, root, true);
-  const hipError_t e = hvdx::launch_bcast_step(rank_ptrs(bufs, nranks), a, vok, st);
+  const hipError_t e = step < 0 ? hvdx::launch_bcast(rank_ptrs(bufs, nranks), a, st)
+                                : hvdx::launch_bcast_step(rank_ptrs(bufs, nranks), a, vok, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "broadcast step launch");
 }
 
@@ -1232,6 +1234,7 @@ static int check_bcast_tensors(const void* const* ptrs, const int64_t* nbytes, c
   return HVDX_OK;
 }
 
+// Chain step `step`, or, for step < 0, the whole broadcast in one launch.
 static int bcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, const int64_t* voffset, int ntensors,
                               int64_t total_bytes, int nranks, int root, int step, hipStream_t st) {
   hvdx::BcastTensorsArgs a{};
@@ -1248,7 +1251,7 @@ static int bcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, co
   a.rem = units % nranks;
   TimedLaunch timed(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, total_bytes, st, root);
   TimedLaunch timed_phase(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, total_bytes, st, root, true);
-  const hipError_t e = hvdx::launch_bcast_tensors_step(a, st);
+  const hipError_t e = step < 0 ? hvdx::launch_bcast_tensors(a, st) : hvdx::launch_bcast_tensors_step(a, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "tensor broadcast step launch");
 }
 
@@ -1268,23 +1271,16 @@ int hvdx_broadcast_tensors(const void* const* ptrs, const int64_t* nbytes, const
                            int64_t total_bytes, int nranks, int root, void* stream) {
   int rc = check_bcast_tensors(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, "hvdx_broadcast_tensors");
   if (rc) return rc;
-  if (total_bytes == 0 || ntensors == 0) return HVDX_OK;
-  for (int s = 0; s < 2 * nranks - 2; ++s) {
-    rc = bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, s,
+  if (total_bytes == 0 || ntensors == 0 || nranks == 1) return HVDX_OK;
+  return bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, -1,
                             static_cast<hipStream_t>(stream));
-    if (rc) return rc;
-  }
-  return HVDX_OK;
 }
 
 int hvdx_broadcast(void* const* bufs, int nranks, int64_t nbytes, int root, void* stream) {
   int rc = check_bcast(bufs, nranks, nbytes, root, "hvdx_broadcast");
   if (rc) return rc;
-  for (int s = 0; nbytes > 0 && s < 2 * nranks - 2; ++s) {
-    rc = bcast_step(bufs, nranks, nbytes, root, s, static_cast<hipStream_t>(stream));
-    if (rc) return rc;
-  }
-  return HVDX_OK;
+  if (nbytes == 0 || nranks == 1) return HVDX_OK;
+  return bcast_step(bufs, nranks, nbytes, root, -1, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

@@ -170,6 +170,24 @@ struct BcastArgs {
   int64_t q, rem;  // 16-byte units per chunk: q, the first rem chunks one more
 };
 hipError_t launch_bcast_step(const RankPtrs& bufs, const BcastArgs& a, bool vector_ok, hipStream_t stream);
+// The whole broadcast in one launch (broadcast_kernels.hip, fusion_kernels.hip for many tensors):
+// 16-byte units per lane, and an LDS reservation that holds the wavefronts per CU down.  Few
+// ranks leave a wavefront little to store for what it has to find first (ResNet-50 to 2 ranks 66 us
+// with one unit, 44 with two, 39 with four; small lists gain nothing: 1.2 MB to 3 ranks 6.0, 6.1
+// and 6.9 us); many ranks are many streams at once, which like little in flight (VGG-16 to 32
+// ranks 3.41 ms with two units, 3.43 with one, 3.19 with one and 12 wavefronts per CU; ResNet-50 to
+// 8 ranks 151 us with two, 145 with two and 16).
+struct BcastShape {
+  int units;
+  unsigned lds;
+};
+inline BcastShape bcast_shape(int nranks, int64_t bytes) {
+  if (nranks > 16) return {1, (160u << 10) / 12 / 512 * 512 - 512};
+  if (nranks <= 4 && bytes >= (32 << 20)) return {4, 0};
+  return {2, nranks <= 4 ? 0u : (160u << 10) / 16 / 512 * 512 - 512};
+}
+constexpr int64_t kBcastRow = 1 << 22;  // blocks in a row of the grid, when there are more than one row
+hipError_t launch_bcast(const RankPtrs& bufs, const BcastArgs& a, hipStream_t stream);  // a.step, q, rem not used
 
 // One chain step of a broadcast of many tensors (fusion_kernels.hip): the chain runs over
 // a virtual byte space in which tensor t occupies [voff[t], voff[t] + nbytes[t]).
@@ -183,6 +201,8 @@ struct BcastTensorsArgs {
   int64_t q, rem;           // 16-byte units per chunk: q, the first rem chunks one more
 };
 hipError_t launch_bcast_tensors_step(const BcastTensorsArgs& a, hipStream_t stream);
+// The whole broadcast in one launch (a.step is not used).
+hipError_t launch_bcast_tensors(const BcastTensorsArgs& a, hipStream_t stream);
 
 // Launchers (fusion_kernels.hip).  With `ring` (nranks >= 3), the copy-in also does
 // the ring's adding step 0 (and with `skip_sender` leaves out each chunk's sender's

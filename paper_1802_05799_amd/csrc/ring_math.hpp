@@ -12,6 +12,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
+// An address known to be global memory: pointers out of a table would otherwise be accessed
+// by flat instructions, which cannot be waited for one after the other.
+template <typename T>
+using Global = T __attribute__((address_space(1)))*;
+
 template <typename T>
 struct Vec;
 template <>
