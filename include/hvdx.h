@@ -401,23 +401,26 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
  * Schedule: chunk c (of N near-equal contiguous chunks, the first count mod N
  * one element longer) moves from rank (c+s) mod N to (c+s+1) mod N in adding
  * step s and from rank (c-1+s) mod N to (c+s) mod N in replacing step s, so the
- * sum of chunk c is formed in ring order starting at rank c.  (Adding step N-2
- * and replacing step 0 run as one kernel here; the buffers end the same.)  Each addition is
+ * sum of chunk c is formed in ring order starting at rank c.  Each addition is
  * rounded to nearest even in dtype (binary16 when compressed); AVERAGE divides
  * the complete sum by nranks once, correctly rounded, at the last adding step.
+ *
+ * hvdx_ring_allreduce runs all of it in one launch: an element's ring never involves another
+ * element, so a lane takes its elements through every step, the messages in registers (2N
+ * elements moved per element; the workspace is checked but not used).
+ * hvdx_ring_allreduce_steps runs a launch per step, the messages through the buffers (and the
+ * workspace), for tracing: every step then has its record in a timeline.  (Adding step N-2
+ * and replacing step 0 run as one kernel there; the buffers end the same.)  Same bits.
  * Errors: HVDX_ERR_INVALID, HVDX_ERR_ALIAS, HVDX_ERR_WORKSPACE, HVDX_ERR_HIP.
  */
 int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                         void* workspace, size_t workspace_bytes, void* stream);
+int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * hvdx_ring_allreduce_small -- hvdx_ring_allreduce without compression, in one
- * launch: each lane runs all 2(N-1) steps (same schedule, same order of additions) for
- * one 16-byte vector of every rank buffer, or for one element where a chunk ends inside
- * a vector, the messages in registers: every rank's value is read once and the result
- * written to every rank.  Same result, bit for bit.  Meant for buffers of at most
- * HVDX_SMALL_BUCKET_BYTES; any size works, and since it moves 2N elements per element
- * instead of 5N-6, any size is faster than a launch per step.
+ * hvdx_ring_allreduce_small -- hvdx_ring_allreduce without compression and so without a
+ * workspace argument.
  * Arguments and errors as hvdx_ring_allreduce with compress = HVDX_COMPRESS_NONE.
  */
 int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int dtype, int op, void* stream);
@@ -425,36 +428,27 @@ int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int 
 /*
  * hvdx_ring_allreduce_noalloc -- hvdx_ring_allreduce for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc): the same kernels, the same result bit for bit, but the
- * compression workspace is a static array inside the library instead of an argument.
- * The call allocates nothing (no hipMalloc, hipFree or allocating library routine).
+ * forbid hipMalloc): no workspace argument, compressed or not; the same kernel, the same
+ * result bit for bit.  The call allocates nothing and keeps nothing.
  *
  *   bufs, nranks, count, dtype, op, compress, stream   as hvdx_ring_allreduce
  *
  * Limit: hvdx_ring_workspace_bytes(nranks, count, dtype, compress) must not exceed
  * hvdx_ring_noalloc_max_bytes() (64 MiB: e.g. 8 ranks of up to 4,194,304 binary32
  * elements compressed); larger requests return HVDX_ERR_WORKSPACE before any HIP
- * call.  Without compression no workspace is used and any size works.
- * The static array is held by every GPU the library runs on until the process ends;
- * its device address is looked up on the first call per device (the stream's device,
- * or the current device for the null stream).  Nothing in it needs to start at zero
- * (every wire element a step reads was written by an earlier step of the same call),
- * and it keeps the last call's contents.  All calls on one GPU share the array:
- * calls that overlap in time on one GPU (on different streams, or from different
- * threads) race; serialize them on one stream.
- * Errors: as hvdx_ring_allreduce; HVDX_ERR_WORKSPACE beyond the limit;
- * HVDX_ERR_UNSUPPORTED on a device index of 64 or more.
+ * call.  Without compression any size works.
+ * Errors: as hvdx_ring_allreduce; HVDX_ERR_WORKSPACE beyond the limit.
  */
 int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                                 void* stream);
-/* Bytes of the static compression workspace behind hvdx_ring_allreduce_noalloc. */
+/* The limit of hvdx_ring_allreduce_noalloc. */
 size_t hvdx_ring_noalloc_max_bytes(void);
 
 /*
  * hvdx_ring_reduce_scatter / hvdx_ring_allgather -- the two halves of
  * hvdx_ring_allreduce (paper section 3: the N-1 adding iterations, then the N-1
- * replacing iterations), each one call.  Running the first and then the second
- * with the same arguments and workspace is hvdx_ring_allreduce.
+ * replacing iterations), each one call and a launch per step.  Running the first and then
+ * the second with the same arguments and workspace gives hvdx_ring_allreduce's result.
  *
  * After the reduce-scatter half, rank (c-1) mod N holds chunk c of the reduced
  * result (with AVERAGE already divided) -- in its buffer, or, when compressing,
@@ -475,8 +469,8 @@ int hvdx_ring_allgather(void* const* bufs, int nranks, int64_t count, int dtype,
  * hvdx_ring_step -- one step of hvdx_ring_allreduce (all N transfers of adding or
  * replacing step `step`, 0 <= step < nranks-1), for tracing and for checking
  * intermediate states.  Running phase REDUCE_SCATTER steps 0..N-2 then
- * ALLGATHER steps 0..N-2 in order, with the same arguments and workspace, is
- * hvdx_ring_allreduce for nranks >= 2.  Arguments as hvdx_ring_allreduce.
+ * ALLGATHER steps 0..N-2 in order, with the same arguments and workspace, gives
+ * hvdx_ring_allreduce's result for nranks >= 2.  Arguments as hvdx_ring_allreduce.
  */
 int hvdx_ring_step(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress, int phase,
                    int step, void* workspace, size_t workspace_bytes, void* stream);
@@ -590,8 +584,8 @@ int hvdx_ring_chunk(int64_t count, int nranks, int c, int64_t* start, int64_t* l
 #define HVDX_KERNEL_FOLD 7      /* hvdx_fold_allreduce */
 #define HVDX_KERNEL_PACK_RS 8   /* copy-in with adding step 0 (step = 0) */
 #define HVDX_KERNEL_AG_UNPACK 9 /* replacing step N-2 with copy-out (step = N-2) */
-#define HVDX_KERNEL_RING_SMALL 10  /* hvdx_ring_allreduce_small: every step in one launch */
-#define HVDX_KERNEL_CYCLE_SMALL 11 /* hvdx_fuse_allreduce_small: copy-in, ring, copy-out in one launch */
+#define HVDX_KERNEL_RING_SMALL 10  /* hvdx_ring_allreduce(_small, _noalloc): every step in one launch */
+#define HVDX_KERNEL_CYCLE_SMALL 11 /* hvdx_fuse_cycle, hvdx_fuse_allreduce_small: whole cycles in one launch */
 
 typedef struct hvdx_trace_record {
   int32_t kind;     /* HVDX_KERNEL_* */

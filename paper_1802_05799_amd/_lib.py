@@ -47,6 +47,7 @@ _SIGNATURES = {
     "hvdx_fuse_cycle_table": (_i64, [_p, _p, _p, _p, _p, _i, _i, _i, _i, _i, _p, _i64, _pi64]),
     "hvdx_fuse_cycle": (_i, [_p, _i, _i64, _i64, _i, _i, _i, _i, _i, _p]),
     "hvdx_ring_allreduce": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
+    "hvdx_ring_allreduce_steps": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
     "hvdx_ring_allreduce_small": (_i, [_pp, _i, _i64, _i, _i, _p]),
     "hvdx_ring_allreduce_noalloc": (_i, [_pp, _i, _i64, _i, _i, _i, _p]),
     "hvdx_ring_noalloc_max_bytes": (_sz, []),
@@ -333,6 +334,12 @@ def hvdx_ring_allreduce(bufs, nranks: int, count: int, dtype: int, op: int, comp
                         workspace: int = 0, workspace_bytes: int = 0, stream: int = 0) -> None:
     pb, _keep = _ptr_array(bufs)
     _check(lib.hvdx_ring_allreduce(pb, nranks, count, dtype, op, compress, workspace, workspace_bytes, stream))
+
+
+def hvdx_ring_allreduce_steps(bufs, nranks: int, count: int, dtype: int, op: int, compress: int = COMPRESS_NONE,
+                              workspace: int = 0, workspace_bytes: int = 0, stream: int = 0) -> None:
+    pb, _keep = _ptr_array(bufs)
+    _check(lib.hvdx_ring_allreduce_steps(pb, nranks, count, dtype, op, compress, workspace, workspace_bytes, stream))
 
 
 def hvdx_ring_allreduce_noalloc(bufs, nranks: int, count: int, dtype: int, op: int, compress: int = COMPRESS_NONE,

@@ -284,45 +284,6 @@ int check_fusion(const void* const* tensors, const int64_t* numel, const int64_t
 
 }  // namespace
 
-// ---- the ring without a caller-provided workspace --------------------------------------
-//
-// The compressed ring's binary16 wire copies live in `scratch`, a static device array
-// that the code object carries (one copy per GPU the library runs on, held until the
-// process ends).  Its device address is looked up once per device, with that device
-// current, and kept; host code never passes the array's own name to a kernel (on the
-// host that name is only a stand-in for the device symbol).
-namespace {
-constexpr size_t kScratchBytes = (size_t)64 << 20;
-__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kScratchBytes];
-constexpr int kScratchDevices = 64;
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[kScratchDevices] = {};
-
-int scratch_for(hipStream_t st, void** out, const char* what) {
-  int dev = -1;
-  hipError_t e = st ? hipStreamGetDevice(st, &dev) : hipGetDevice(&dev);
-  if (e != hipSuccess) return hip_fail(e, "static workspace: the stream's device");
-  if (dev < 0 || dev >= kScratchDevices)
-    return fail(HVDX_ERR_UNSUPPORTED, "%s: device %d beyond the %d this build serves", what, dev, kScratchDevices);
-  std::lock_guard<std::mutex> g(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    int cur = -1;
-    e = hipGetDevice(&cur);
-    if (e != hipSuccess) return hip_fail(e, "static workspace: hipGetDevice");
-    if (cur != dev && (e = hipSetDevice(dev)) != hipSuccess) return hip_fail(e, "static workspace: hipSetDevice");
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (cur != dev) (void)hipSetDevice(cur);
-    if (e != hipSuccess) return hip_fail(e, "static workspace: hipGetSymbolAddress");
-    if (!p || (reinterpret_cast<uintptr_t>(p) & 255))
-      return fail(HVDX_ERR_HIP, "%s: static workspace address %p is not 256-byte aligned", what, p);
-    g_scratch_ptr[dev] = p;
-  }
-  *out = g_scratch_ptr[dev];
-  return HVDX_OK;
-}
-}  // namespace
-
 extern "C" {
 
 int hvdx_version(void) { return HVDX_VERSION; }
@@ -593,6 +554,17 @@ int hvdx_ring_allgather(void* const* bufs, int nranks, int64_t count, int dtype,
                    stream, "hvdx_ring_allgather");
 }
 
+// The whole ring in one launch (arguments already checked, nranks >= 2, count > 0).
+static int run_whole_ring(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+                          hipStream_t st) {
+  TimedLaunch timed(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, compress, count, st);
+  TimedLaunch timed_phase(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, compress, count, st, -1, true);
+  const hipError_t e = hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), dtype,
+                                              compress == HVDX_COMPRESS_FP16 ? HVDX_FLOAT16 : dtype,
+                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
+  return e == hipSuccess ? HVDX_OK : hip_fail(e, "one-launch ring");
+}
+
 int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                         void* workspace, size_t workspace_bytes, void* stream) {
   int rc = check_ring(bufs, nranks, count, dtype, op, compress, workspace, workspace_bytes, "hvdx_ring_allreduce");
@@ -601,6 +573,18 @@ int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   if (nranks == 1)
     return run_phase(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, workspace,
                      workspace_bytes, stream, "hvdx_ring_allreduce");
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
+}
+
+int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+                              void* workspace, size_t workspace_bytes, void* stream) {
+  static const char* what = "hvdx_ring_allreduce_steps";
+  int rc = check_ring(bufs, nranks, count, dtype, op, compress, workspace, workspace_bytes, what);
+  if (rc) return rc;
+  if (count == 0) return HVDX_OK;
+  if (nranks == 1)
+    return run_phase(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, workspace,
+                     workspace_bytes, stream, what);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int last = nranks - 2;
   rc = run_steps(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, 0, last, workspace, st);
@@ -1120,12 +1104,7 @@ int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int 
   int rc = check_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, nullptr, 0, "hvdx_ring_allreduce_small");
   if (rc) return rc;
   if (count == 0 || nranks == 1) return HVDX_OK;  // no messages; AVERAGE divides by 1
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  TimedLaunch timed(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, HVDX_COMPRESS_NONE, count, st);
-  TimedLaunch timed_phase(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, HVDX_COMPRESS_NONE, count, st, -1, true);
-  const hipError_t e = hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), dtype, dtype,
-                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
-  return e == hipSuccess ? HVDX_OK : hip_fail(e, "one-launch ring");
+  return run_whole_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, static_cast<hipStream_t>(stream));
 }
 
 int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
@@ -1147,7 +1126,7 @@ int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "fold launch");
 }
 
-size_t hvdx_ring_noalloc_max_bytes(void) { return kScratchBytes; }
+size_t hvdx_ring_noalloc_max_bytes(void) { return (size_t)64 << 20; }
 
 int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                                 void* stream) {
@@ -1159,17 +1138,14 @@ int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, in
     return fail(HVDX_ERR_INVALID, "%s: unknown compression %d", what, compress);
   if (compress == HVDX_COMPRESS_FP16 && dtype != HVDX_FLOAT32)
     return fail(HVDX_ERR_INVALID, "%s: fp16 compression needs float32 buffers", what);
-  const size_t need = hvdx_ring_workspace_bytes(nranks, count, dtype, compress);
-  if (need > kScratchBytes)
-    return fail(HVDX_ERR_WORKSPACE, "%s: %d ranks of %lld elements need %zu bytes of wire workspace; the static one "
-                "holds %zu (use hvdx_ring_allreduce with a workspace)", what, nranks, (long long)count, need,
-                kScratchBytes);
-  if (need == 0)  // nothing compressed: no workspace at all
+  const size_t need = hvdx_ring_workspace_bytes(nranks, count, dtype, compress), most = hvdx_ring_noalloc_max_bytes();
+  if (need > most)
+    return fail(HVDX_ERR_WORKSPACE, "%s: %d ranks of %lld elements need %zu bytes of wire workspace; the static limit "
+                "is %zu (use hvdx_ring_allreduce with a workspace)", what, nranks, (long long)count, need, most);
+  if (count == 0) return HVDX_OK;
+  if (nranks == 1)
     return hvdx_ring_allreduce(bufs, nranks, count, dtype, op, compress, nullptr, 0, stream);
-  void* ws = nullptr;
-  rc = scratch_for(static_cast<hipStream_t>(stream), &ws, what);
-  if (rc) return rc;
-  return hvdx_ring_allreduce(bufs, nranks, count, dtype, op, compress, ws, kScratchBytes, stream);
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
 }
 
 static int check_bcast(void* const* bufs, int nranks, int64_t nbytes, int root, const char* what) {

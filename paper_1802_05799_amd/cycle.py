@@ -286,7 +286,7 @@ class FusedAllreduce:
         elif self.schedule == "fold":
             L.hvdx_fold_allreduce(ptrs, self.nranks, count, dtype, self.op, compress, stream)
         else:
-            L.hvdx_ring_allreduce(ptrs, self.nranks, count, dtype, self.op, compress, ws, wsb, stream)
+            L.hvdx_ring_allreduce_steps(ptrs, self.nranks, count, dtype, self.op, compress, ws, wsb, stream)
 
     def ring_phase(self, b: Bucket, phase: int, stream: int) -> None:
         """All N-1 steps of one half of the ring (one C call)."""
