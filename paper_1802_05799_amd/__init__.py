@@ -74,7 +74,7 @@ from ._lib import (  # noqa: F401
     hvdx_timeline_end,
     hvdx_version,
 )
-from .cycle import FusedAllreduce  # noqa: F401
+from .cycle import FusedAllreduce, current_stream  # noqa: F401
 from .timeline import Timeline  # noqa: F401
 
 
@@ -145,7 +145,7 @@ class TensorBroadcast:
 
     def _stream(self, stream):
         if stream is None:
-            stream = torch.cuda.current_stream(self.device).cuda_stream
+            stream = current_stream(self.device)
         if stream not in self._waited:  # once per stream: the tables' upload precedes the first launch
             torch.cuda.ExternalStream(stream, device=self.device).wait_event(self._ready)
             self._waited.add(stream)

@@ -43,6 +43,12 @@ _HVDX_DTYPE = {torch.float32: L.FLOAT32, torch.float16: L.FLOAT16}
 _OPS = {"sum": L.SUM, "average": L.AVERAGE}
 
 
+def current_stream(device: torch.device) -> int:
+    """The handle of torch's current stream on a device, without the Stream object that
+    torch.cuda.current_stream builds around it (2.0 us of the 5.9 of a small call)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 @dataclass
 class Bucket:
     tensors: list  # indices into the ready list
@@ -403,7 +409,7 @@ class FusedAllreduce:
 
     def __call__(self, stream: int | None = None) -> None:
         if stream is None:
-            stream = torch.cuda.current_stream(self.device).cuda_stream
+            stream = current_stream(self.device)
         if self._cycles is not None:
             for c in self._cycles:
                 L.hvdx_fuse_cycle(*c.args, stream)
