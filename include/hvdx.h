@@ -356,15 +356,15 @@ int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t cou
 /*
  * hvdx_fuse_allreduce_small -- hvdx_fuse_allreduce for small fusion buffers: the same
  * result, bit for bit, in one kernel launch instead of 2N-1.  Each thread takes a
- * 16-byte stretch of the buffer (element by element where it meets a tensor edge)
- * through the copy-in for every rank (paper section 7, step 3), all 2(N-1) steps of
- * the ring of paper section 3 in their order -- each step reading the sender's
- * buffer and writing the receiver's -- and the copy-out (step 5).  An element's ring
- * never involves another element, so its steps need not wait for the rest of the
- * buffer.  Intended for buffers of at most HVDX_SMALL_BUCKET_BYTES per rank, where
- * the per-step launches cost more than their data; any size works.
+ * 16-byte stretch of the buffer's layout (element by element where it meets a tensor edge)
+ * from every rank's tensors through all 2(N-1) steps of the ring of paper section 3 in their
+ * order, the messages in registers, and stores the result to every rank's tensors.  An
+ * element's ring never involves another element, so its steps need not wait for the rest
+ * of the buffer.  Intended for buffers of at most HVDX_SMALL_BUCKET_BYTES per rank whose
+ * descriptors are on the GPU already; any size works (hvdx_fuse_cycle, with a table made on
+ * the host, is faster at every size).
  * Arguments, ownership and errors as hvdx_fuse_allreduce (any nranks >= 1); the
- * fusion buffers are scratch afterwards (padding is not written).
+ * fusion buffers are checked but not used.
  */
 int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const int64_t* offset, int ntensors,
                               int tensor_dtype, void* const* bufs, int64_t buf_count, int buf_dtype, int nranks,

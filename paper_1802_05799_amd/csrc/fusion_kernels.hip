@@ -714,11 +714,12 @@ __global__ __launch_bounds__(Cfg::BS) HVDX_COPY_ATTR void unpack_pair_kernel(Cop
 
 // ---- a small fusion buffer's whole cycle in one launch ------------------------------
 //
-// For buffers so small that launches cost more than their data: each thread takes one
-// 16-byte buffer vector through the copy-in for every rank, all 2(N-1) ring steps
-// (ring_chain: each step reads the sender's buffer and writes the receiver's) and the
-// copy-out for every rank.  Vectors of padding only are skipped (their values never
-// reach a tensor and the buffers are scratch afterwards); edge vectors go element by
+// For callers with device descriptors and no table (hvdx_fuse_cycle's is the faster): each
+// thread takes one 16-byte buffer vector of every rank's tensors through all 2(N-1) ring steps
+// in registers and stores the result to every rank's.  The bound is latency: with each step's
+// message through the buffers a thread waited for 2(N-1) memory round trips one after the other
+// (15.9 us for the toy list on 4 ranks); now the loads go out eight ranks at a time.  Vectors of
+// padding only are skipped; edge vectors and those that cross a chunk end go element by
 // element.  A block serves one tile of 256 vectors for all ranks.
 using SmallCfg = CopyCfg<1, 1, 0, false, false>;
 
@@ -726,7 +727,7 @@ template <typename TT, typename TB, int DIV>
 __global__ __launch_bounds__(kBlock) void small_cycle_kernel(const void* const* __restrict__ tensors,
                                                              const int64_t* __restrict__ numel,
                                                              const int64_t* __restrict__ offset, int ntensors,
-                                                             RankPtrs bufs, RingArgs a, int64_t count) {
+                                                             RingArgs a, int64_t count) {
   using Cfg = SmallCfg;
   using M = Mover<TT, TB>;
   using VB = typename M::buf_vec;
@@ -742,19 +743,35 @@ __global__ __launch_bounds__(kBlock) void small_cycle_kernel(const void* const* 
                                                     s_end, s_meta, s_ptr, &pin);
   const PtrTable pt{tensors, pin ? s_ptr : nullptr, tt.t0, ntensors, tt.nt, 0, 0, n};
   const Pos ps = classify<V>(tt, s_off, s_end, offset, numel, p0 + (int64_t)threadIdx.x * V, p1, 0, count);
-  auto buf = [&](int r) { return static_cast<TB*>(bufs.p[r]); };
-  auto ten = [&](int r, int64_t t) { return static_cast<TT*>(const_cast<void*>(pt.get(r, t))); };
-  if (ps.cls == POS_VEC) {
-    for (int r = 0; r < n; ++r)
-      st16<false>(reinterpret_cast<VB*>(buf(r) + ps.p), M::template load<false>(ten(r, ps.t) + ps.li));
-    const int64_t c0 = chunk_index(ps.p, a);
-    if (chunk_index(ps.p + V - 1, a) == c0) {
-      ring_chain<TB, VB, DIV>(bufs, ps.p, (int)c0, a);
-    } else {
-      for (int k = 0; k < V; ++k) ring_chain<TB, TB, DIV>(bufs, ps.p + k, (int)chunk_index(ps.p + k, a), a);
+  // The ring of what `load` finds at (rank, tensor t), from rank c on, in its order.
+  auto ring = [&](int c, auto load, auto store) {
+    auto rank = [&](int k) { return c + k < n ? c + k : c + k - n; };
+    constexpr int R = 8;
+    auto sum = load(rank(0));
+    for (int k0 = 1; k0 < n; k0 += R) {
+      decltype(sum) x[R];
+#pragma unroll
+      for (int k = 0; k < R; ++k) x[k] = load(rank(k0 + k < n ? k0 + k : n - 1));
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        if (k0 + k < n - 1) sum = add_step<DIV_NONE>(x[k], sum, a);
+        else if (k0 + k == n - 1) sum = add_step<DIV>(x[k], sum, a);
+      }
     }
-    for (int r = 0; r < n; ++r)
-      M::template store<false>(ten(r, ps.t) + ps.li, *reinterpret_cast<const VB*>(buf(r) + ps.p));
+    for (int r = 0; r < n; ++r) store(r, sum);
+  };
+  auto ten = [&](int r, int64_t t) { return static_cast<TT*>(const_cast<void*>(pt.get(r, t))); };
+  auto element = [&](int64_t t, int64_t li, int64_t p) {
+    ring((int)chunk_index(p, a), [&](int r) { return M::cvt_in(ten(r, t)[li]); },
+         [&](int r, TB v) { ten(r, t)[li] = M::cvt_out(v); });
+  };
+  if (ps.cls == POS_VEC) {
+    const int64_t c0 = chunk_index(ps.p, a);
+    if (chunk_index(ps.p + V - 1, a) == c0)
+      ring((int)c0, [&](int r) { return M::template load<false>(ten(r, ps.t) + ps.li); },
+           [&](int r, VB v) { M::template store<false>(ten(r, ps.t) + ps.li, v); });
+    else
+      for (int k = 0; k < V; ++k) element(ps.t, ps.li + k, ps.p + k);
   } else if (ps.cls == POS_EDGE) {
     for (int k = 0; k < V; ++k) {
       const int64_t pe = ps.p + k;
@@ -762,10 +779,7 @@ __global__ __launch_bounds__(kBlock) void small_cycle_kernel(const void* const* 
       const int jk = lookup(tt, s_off, offset, pe);
       const int64_t tk = tt.t0 + jk;
       if (tk < 0 || pe >= tensor_end(tt, s_end, offset, numel, jk)) continue;  // padding
-      const int64_t li = pe - tensor_begin(tt, s_off, offset, jk);
-      for (int r = 0; r < n; ++r) buf(r)[pe] = M::cvt_in(ten(r, tk)[li]);
-      ring_chain<TB, TB, DIV>(bufs, pe, (int)chunk_index(pe, a), a);
-      for (int r = 0; r < n; ++r) ten(r, tk)[li] = M::cvt_out(buf(r)[pe]);
+      element(tk, pe - tensor_begin(tt, s_off, offset, jk), pe);
     }
   }
 }
@@ -1456,12 +1470,12 @@ hipError_t launch_unpack_pair(const CopyPair& m, int buf_dtype, int dst_dtype, i
 }
 
 hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, const int64_t* offset, int ntensors,
-                              int tensor_dtype, const RankPtrs& bufs, const RingArgs& a, int64_t count, int buf_dtype,
-                              int divmode, hipStream_t stream) {
+                              int tensor_dtype, const RingArgs& a, int64_t count, int buf_dtype, int divmode,
+                              hipStream_t stream) {
   const dim3 grid(tiles_for<SmallCfg>(count, vec_elems(tensor_dtype, buf_dtype))), block(kBlock);
 #define HVDX_SMALL(TT, TB, DIV) \
-  HVDX_LAUNCH((small_cycle_kernel<TT, TB, DIV>), grid, block, 0, stream, tensors, numel, offset, ntensors, \
-                     bufs, a, count)
+  HVDX_LAUNCH((small_cycle_kernel<TT, TB, DIV>), grid, block, 0, stream, tensors, numel, offset, ntensors, a, \
+              count)
 #define HVDX_SMALL_D(TT, TB) \
   if (divmode == DIV_NONE) { HVDX_SMALL(TT, TB, DIV_NONE); } \
   else if (divmode == DIV_POW2) { HVDX_SMALL(TT, TB, DIV_POW2); } \

@@ -1095,8 +1095,7 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
                           true);
   const hipError_t e =
       hvdx::launch_small_cycle(const_cast<const void* const*>(tensors), numel, offset, ntensors, tensor_dtype,
-                               rank_ptrs(bufs, nranks), ring_args(nranks, buf_count, 0), buf_count, buf_dtype,
-                               div_mode(op, nranks), st);
+                               ring_args(nranks, buf_count, 0), buf_count, buf_dtype, div_mode(op, nranks), st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "small cycle launch");
 }
 

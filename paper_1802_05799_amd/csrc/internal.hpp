@@ -138,8 +138,8 @@ hipError_t launch_ag_tiles(const TiledRing& k, int tensor_dtype, int buf_dtype, 
 hipError_t launch_add_tiles(const TiledRing& k, int tensor_dtype, int buf_dtype, int step, hipStream_t stream);
 // A small fusion buffer's copy-in, ring and copy-out in one launch.
 hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, const int64_t* offset, int ntensors,
-                              int tensor_dtype, const RankPtrs& bufs, const RingArgs& a, int64_t count, int buf_dtype,
-                              int divmode, hipStream_t stream);
+                              int tensor_dtype, const RingArgs& a, int64_t count, int buf_dtype, int divmode,
+                              hipStream_t stream);
 
 // The whole ring in one launch (fold_kernels.hip): each lane runs every step for its elements,
 // the messages in registers.  Over flat rank buffers (a holds their partition):

@@ -138,28 +138,5 @@ __device__ __forceinline__ f16x4 add_step(f16x4 local, f16x4 recv, const RingArg
   return combine<DIV>(local, recv, a);
 }
 
-// The whole ring for the elements at e (one T, or one 16-byte vector A of them, all in
-// chunk c), in the ring's order: adding steps 0..N-2, then replacing steps 0..N-2, each
-// reading the sender's buffer and writing the receiver's.  Elements never meet other
-// elements on the ring, so one thread can run an element's steps back to back.
-template <typename T, typename A, int DIV>
-__device__ __forceinline__ void ring_chain(const RankPtrs& bufs, int64_t e, int c, const RingArgs& a) {
-  auto at = [&](int r) { return reinterpret_cast<A*>(static_cast<T*>(bufs.p[r]) + e); };
-  const int n = a.n;
-  int snd = c;  // adding step s: chunk c goes from rank c+s to c+s+1
-  for (int s = 0; s < n - 1; ++s) {
-    const int rcv = snd + 1 == n ? 0 : snd + 1;
-    const A x = *at(snd);
-    A* pr = at(rcv);
-    *pr = s == n - 2 ? add_step<DIV>(*pr, x, a) : add_step<DIV_NONE>(*pr, x, a);
-    snd = rcv;
-  }
-  for (int s = 0; s < n - 1; ++s) {  // snd is the owner, c-1; replacing step s: c-1+s to c+s
-    const int rcv = snd + 1 == n ? 0 : snd + 1;
-    *at(rcv) = *at(snd);
-    snd = rcv;
-  }
-}
-
 }  // namespace
 }  // namespace hvdx
