@@ -122,12 +122,11 @@ class TensorBroadcast:
         self.device = flat[0].device if flat else torch.device("cuda", torch.cuda.current_device())
         voff, self.total = hvdx_broadcast_layout(nbytes[0].tolist() if nt else [])
         # The whole call is one launch, whose wavefronts take stretches of the virtual space: its own
-        # layout starts each tensor where rank 0's address lies in a 4 KiB page, so that the
-        # stretches end with the tensors' cache lines
+        # layout starts each tensor in a 4 KiB page of its own, where rank 0's address lies in one,
+        # so that a stretch has one tensor and ends with its cache lines
         starts0, at = [], 0
         for p, k in zip(ptr[:nt].tolist(), nbytes[0].tolist()):
-            at = -(-at // 16) * 16
-            at += (p - at) % 4096
+            at = -(-at // 4096) * 4096 + p % 4096
             starts0.append(at)
             at += k
         # one upload: the rank-major pointer table, then the byte counts, then both layouts' starts
