@@ -9,12 +9,13 @@
 // Bound: HBM, N read and N write streams at once.  What the shape has to get right is how
 // much is in flight.  Measured on MI355X (N buffers, in place, binary32):
 //   256-thread blocks, full occupancy, 4 loads in flight per lane   4.9 TB/s (N=8), 4.9 (N=32)
-//   one wavefront per block, all ranks' loads in one burst          5.7 TB/s (N=8), 5.25 (N=32)
-//   the same with 8 (N=8) or 6 (N=16, 32) wavefronts per CU         6.25, 6.05, 5.7 TB/s
+//   one wavefront per block, the loads in whole bursts              5.85 (N=8), 5.2 (N=16, 32)
+//   the same with 6 (N=8), 4 (N=16) or 2 (N=32) wavefronts per CU   6.36, 6.22, 6.0
 // (one stream in place: 6.55).  More in flight only spreads the accesses to an HBM page
-// apart in time.  A wavefront that goes on to a second tile loses 10-20%: loads and stores
-// share one in-order counter, so its next loads wait behind its own stores.  Hence one
-// wavefront per block, one 16-byte vector per lane and rank, one burst of loads, the
+// apart in time: some 24 to 40 KiB of loads per CU is best, and the stores, which wait for
+// nothing, follow at once.  A wavefront that goes on to a second tile loses 10-20%: loads and
+// stores share one in-order counter, so its next loads wait behind its own stores.  Hence one
+// wavefront per block, one 16-byte vector per lane and rank, its loads in whole bursts, the
 // stores, and the end; an LDS reservation no one uses holds the wavefronts per CU down.
 #pragma once
 
@@ -131,19 +132,17 @@ __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, 
 #pragma unroll
     for (int j = 0; j < B; ++j) s = F::in(x[j]) + s;
   }
-  constexpr int R = B > 16 ? 16 : B;  // the rest in one or two bursts of up to 16
-#pragma unroll 1
-  for (; k0 < n; k0 += R) {
-    vec x[R];
-    TT* p[R];
+  if (k0 < n) {  // the rest in one more
+    vec x[B];
+    TT* p[B];
     const int left = n - k0, adds = same_count(left);
 #pragma unroll
-    for (int j = 0; j < R; ++j) p[j] = uniform_here(ptr(k0 + j));
+    for (int j = 0; j < B; ++j) p[j] = uniform_here(ptr(k0 + j));
 #pragma unroll
-    for (int j = 0; j < R; ++j)
+    for (int j = 0; j < B; ++j)
       if (j < left) x[j] = __builtin_nontemporal_load(at(p[j]));
 #pragma unroll
-    for (int j = 0; j < R; ++j)
+    for (int j = 0; j < B; ++j)
       if (j < adds) s = F::in(x[j]) + s;
   }
   const MT o = F::out(finish_vec<F::V>(s, a, mode));
@@ -188,31 +187,34 @@ __device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, 
 }
 
 // Wavefronts per SIMD that the registers of a burst have to leave room for.
-constexpr int fold_waves(int burst) { return burst <= 8 ? 4 : burst <= 16 ? 3 : 2; }
+constexpr int fold_waves(int burst) { return burst <= 8 ? 4 : 3; }
 
-// Host side: the loads of a burst for n ranks (one instantiation each).  Every burst should be a
-// whole one: a shorter last one tests before each load.  TB/s, Inception-V3's tensors:
-//   9 ranks   in a burst of up to 16 5.76, of 9 6.12       24   16 + 8 5.44, 2 x 12 5.65
-//   12        in one of up to 16     5.77, of 12 6.03      40   16 + 16 + 8 5.24, 4 x 10 5.50
-//   17        16 + 1                 5.32, 9 + 8 5.62      64   4 x 16 5.41, 2 x 32 5.45
-// So: all ranks up to 16, 32 where it divides n, else the longest of 16 to 8 that divides n,
-// else near-equal ones.
+// Host side: the loads of a burst for n ranks (one instantiation each), and the wavefronts per CU
+// that go with it, as Inception-V3's binary32 tensors measure them (TB/s; a:b is bursts of a with
+// b wavefronts).  Every burst but the last should be a whole one of up to 16: a shorter one tests
+// before each load, and more registers than that leave too few wavefronts to small launches.
+//   7 ranks  7:6 6.44, 4:10 6.39          16  8:4 6.25, 16:3 6.11, 4:6 6.19, 16:8 5.77
+//   8        4:6 6.37, 8:5 6.26, 8:8 6.20 24  12:3 6.09, 8:3 6.06, 16:2 5.59
+//   12       6:5 6.32, 12:3 6.25          40  10:3 5.81, 8:3 5.77, 16:2 5.52
+//   13       7:5 6.21, 13:3 6.28          64  16:2 5.64, 8:3 5.63, 16:4 5.46 (rounded to binary16)
+// So: all ranks below 8; halves up to 24 ranks; then the longest of 16 to 10 that divides n, else
+// near-equal ones of up to 12 (33 ranks: 11:3 5.90, 16:2 5.39).
 inline int fold_burst(int n) {
-  if (n <= 16) return n < 2 ? 2 : n;
-  if (n % 32 == 0) return 32;
-  for (int b = 16; b >= 8; --b)
+  if (n < 8) return n < 2 ? 2 : n;
+  if (n <= 24) return (n + 1) / 2;
+  for (int b = 16; b >= 10; --b)
     if (n % b == 0) return b;
-  const int bursts = (n + 15) / 16;
+  const int bursts = (n + 11) / 12;
   return (n + bursts - 1) / bursts;
 }
 
-// LDS bytes per block that hold the wavefronts per CU down to what streams best with `burst`
-// loads in flight in each: 17 for 4 (6.19 TB/s; 6.0 with 12, 6.11 with 32), 12 for 6 (6.22; 6.04
-// with 10, 5.88 with 20), 10 for 8 (6.13; 6.0 with 14, 5.88 with 32), 8 for 12, 6 for 16 and 32
-// (VGG-16 on 32 ranks 6.28 ms; 6.58 with 5, 6.37 with 8).
-inline unsigned fold_lds(int burst) {
-  if (burst < 4) return 0;
-  const int waves = std::max(6, 3 + (54 + burst / 2) / burst);
+// LDS bytes per block that hold the wavefronts per CU down: all ranks' loads in one burst like some
+// 36 loads in flight per CU (3 ranks 12 wavefronts 6.41, 16 6.32; 4: 10 6.38, 16 6.29; 6: 6 6.49,
+// 10 6.34), several bursts some 28, in at most 6 wavefronts (VGG-16 on 32 ranks 16:2 5.90, 16:3
+// 5.46, 16:6 5.31).  2 ranks like all there is (6.39; 6.24 with 16).
+inline unsigned fold_lds(int n, int burst) {
+  if (burst < 3) return 0;
+  const int waves = burst == n ? (36 + burst - 1) / burst : std::min(6, (28 + burst - 1) / burst);
   return (160u << 10) / waves / 512 * 512 - 512;
 }
 

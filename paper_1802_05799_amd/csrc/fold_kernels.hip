@@ -17,7 +17,7 @@ namespace {
 // run of them (scalar loads, several per instruction).
 
 struct RingPtrs {
-  void* p[2 * HVDX_MAX_RANKS];
+  void* p[2 * HVDX_MAX_RANKS + kFoldPad];
 };
 
 template <typename TT, typename TB, int B>
@@ -38,7 +38,10 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
 // ---- the tensors of a table -------------------------------------------------------------
 //
 // kFoldParts blocks per tile of the table, one per 64*V elements of it; the table lists
-// every tensor's ranks twice over, too.
+// every tensor's ranks twice over, too.  The table is read as constant memory: read as plain
+// memory, a store's pointer is a vector load behind the store before it, and a wavefront's N
+// stores go out one round trip apart (ResNet-50 on 8 ranks 265 us, 256 so; Inception-V3 on 16 510,
+// 486; VGG-16 on 32 6.20 ms, 5.98, in both the bursts and the wavefronts that suit it best).
 
 constexpr int64_t kFoldRow = 1 << 22;  // blocks in a row of the grid, when there are more than one row
 
@@ -48,27 +51,27 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(F
   const int64_t b = (int64_t)blockIdx.y * kFoldRow + blockIdx.x;
   if (b >= t.ntiles * kFoldParts) return;
   typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-  const i32x4 w = reinterpret_cast<const i32x4*>(t.tiles)[b / kFoldParts];  // a FoldTile in one load
+  const i32x4 w = constant(reinterpret_cast<const i32x4*>(t.tiles))[b / kFoldParts];  // a FoldTile in one load
   const uint32_t bits = (uint32_t)w[3];
   const int part = (int)(b % kFoldParts) * S;
   const int left = (int)(bits & 0xffff) - part;
   if (left <= 0) return;
-  void* const* p = t.ptrs + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
+  const auto p = constant(t.ptrs) + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
   const int64_t li = ((int64_t)w[1] << 32 | (uint32_t)w[0]) + part;
   auto ptr = [&](int k) { return static_cast<TT*>(p[k]) + li; };
   fold_stretch<TT, TB, B>(ptr, a, mode, left < S ? left : S, bits >> 24);
 }
 
-// Whether to hold the wavefronts per CU down (fold_lds).  Not where all ranks' elements about fit
-// the 256 MiB Infinity Cache: then a launch is over before HBM pages are what counts, and more
-// wavefronts start faster (6 ranks of 5M binary32 elements 5.58 TB/s held, 5.83 not; of 10M 5.96 and
-// 6.15; of 20M 6.12 and 6.14; 16 ranks of 3M 5.30 and 5.50, of 10M 5.98 and 5.89).  And not where
-// more than 1/8 of the blocks have little or nothing to move (short tensors, each cut into N
-// chunks: Inception-V3's tensors reduced one by one on 16 ranks 605 us held, 580 not).
+// Whether to hold the wavefronts per CU down (fold_lds).  Not in a launch so short that filling the
+// chip is what counts (TB/s held and not: 8 ranks of 1M binary32 elements 4.69, 4.96; of 3M 5.46,
+// 5.44; of 6M 5.87, 5.45; 16 ranks of 0.3M 3.65, 4.06; of 1.5M 5.31, 5.13; 32 of 1.5M 5.36, 5.02; 4
+// of 3M 5.19, 5.30).  And not where more than 1/8 of the blocks have little or nothing to move
+// (short tensors, each cut into N chunks: Inception-V3's tensors reduced one by one on 16 ranks 605
+// us held, 580 not).
 bool fold_holds(int64_t blocks, int64_t count, int nranks, int tensor_dtype) {
   const int64_t bytes = count * (tensor_dtype == HVDX_FLOAT16 ? 2 : 4);
   const int64_t filled = bytes / (kFoldLanes * 16);
-  return bytes > (384ll << 20) / nranks && blocks <= filled + filled / 8;
+  return bytes > (96ll << 20) / nranks && blocks <= filled + filled / 8;
 }
 
 // Calls f(TT{}, TB{}, integral_constant<burst>) for the launch's types and burst.
@@ -78,9 +81,9 @@ void with_burst(int burst, const F& f) {
 #define HVDX_BURST(B) \
   case B: return f(TT{}, TB{}, std::integral_constant<int, B>{});
     HVDX_BURST(2) HVDX_BURST(3) HVDX_BURST(4) HVDX_BURST(5) HVDX_BURST(6) HVDX_BURST(7) HVDX_BURST(8) HVDX_BURST(9)
-    HVDX_BURST(10) HVDX_BURST(11) HVDX_BURST(12) HVDX_BURST(13) HVDX_BURST(14) HVDX_BURST(15) HVDX_BURST(16)
+    HVDX_BURST(10) HVDX_BURST(11) HVDX_BURST(12) HVDX_BURST(13) HVDX_BURST(14) HVDX_BURST(15)
 #undef HVDX_BURST
-    default: return f(TT{}, TB{}, std::integral_constant<int, 32>{});
+    default: return f(TT{}, TB{}, std::integral_constant<int, 16>{});
   }
 }
 template <typename F>
@@ -100,7 +103,7 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
   if (bx > (1 << 22)) bx = 1 << 22;
   const dim3 grid((unsigned)bx, (unsigned)a.n);
   const int burst = fold_burst(a.n);
-  const unsigned lds = fold_holds(bx * a.n, a.q * a.n + a.rem, a.n, tensor_dtype) ? fold_lds(burst) : 0;
+  const unsigned lds = fold_holds(bx * a.n, a.q * a.n + a.rem, a.n, tensor_dtype) ? fold_lds(a.n, burst) : 0;
   RingPtrs ptrs;
   for (int r = 0; r < a.n; ++r) ptrs.p[r] = ptrs.p[a.n + r] = bufs.p[r];
   with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
@@ -116,7 +119,7 @@ hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int64_t coun
   const int64_t bx = blocks < kFoldRow ? blocks : kFoldRow;
   const dim3 grid((unsigned)bx, (unsigned)((blocks + bx - 1) / bx));
   const int burst = fold_burst(a.n);
-  const unsigned lds = fold_holds(blocks, count, a.n, tensor_dtype) ? fold_lds(burst) : 0;
+  const unsigned lds = fold_holds(blocks, count, a.n, tensor_dtype) ? fold_lds(a.n, burst) : 0;
   with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
     HVDX_LAUNCH((fold_table_kernel<decltype(tt), decltype(tb), b.value>), grid, dim3(kFoldLanes), lds, stream, t, a,
                 divmode);

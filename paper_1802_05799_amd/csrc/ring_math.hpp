@@ -17,6 +17,16 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 template <typename T>
 using Global = T __attribute__((address_space(1)))*;
 
+// An address whose contents no launch in flight changes: what all lanes read alike from there
+// goes through scalar loads even after the kernel's first store.  Otherwise a pointer read
+// between two stores is a vector load, whose wait is one for the store before it.
+template <typename T>
+using Constant = const T __attribute__((address_space(4)))*;
+template <typename T>
+__device__ __forceinline__ Constant<T> constant(const T* p) {
+  return (Constant<T>)reinterpret_cast<uint64_t>(p);
+}
+
 template <typename T>
 struct Vec;
 template <>

@@ -20,7 +20,7 @@ By default all of that runs in one launch for every fusion buffer and one for ev
 reduced by itself (hvdx_fuse_cycle): each lane takes its elements through all 2(N-1)
 steps of the ring in their order, the messages in registers, so an element is read once
 and written once per rank, 2N elements moved instead of the 5N-6 of a launch per step
-(VGG-16 on 32 ranks: 12.9 ms in steps, 6.2 ms in one launch).  An argument that asks for
+(VGG-16 on 32 ranks: 12.9 ms in steps, 6.0 ms in one launch).  An argument that asks for
 the steps themselves (see FusedAllreduce) gets a launch, and a timeline record, per step;
 buckets of at most `small_bucket_bytes` per rank then still run in one launch
 (hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small).  Fused buckets on the per-step path

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16], ids=["f32", "f16"])
-@pytest.mark.parametrize("n", [2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 128])
+@pytest.mark.parametrize("n", [2, 7, 8, 9, 15, 16, 17, 24, 25, 27, 30, 31, 32, 33, 48, 63, 64, 65, 127, 128])
 def test_flat_buffers(n, dtype):
     stretch = 64 * 16 // np.dtype(dtype).itemsize
     rng = np.random.default_rng(5000 + n)
