@@ -370,10 +370,11 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
                               int tensor_dtype, void* const* bufs, int64_t buf_count, int buf_dtype, int nranks,
                               int op, void* stream);
 
-/* Per-rank buffer bytes at or below which a fusion buffer's (or a tensor's) whole ring
- * costs less in one launch (hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small) than
- * in one launch per step on MI355X: below it a step's messages take less time than
- * launching the step.  A recommendation for callers; the library does not switch. */
+/* Per-rank buffer bytes at or below which the launch-per-step path of FusedAllreduce runs a
+ * fusion buffer (or a tensor) in one launch all the same (hvdx_fuse_allreduce_small,
+ * hvdx_ring_allreduce_small): its messages take less time than launching a step does.  One
+ * launch is the faster at every size (hvdx_fuse_cycle, hvdx_ring_allreduce); the steps are
+ * there for callers that want them one by one.  The library does not switch. */
 #define HVDX_SMALL_BUCKET_BYTES (4 << 20)
 
 /*
