@@ -249,6 +249,10 @@ class FusedAllreduce:
                 sets = [[torch.empty(max(c, 1) if k == 0 else c, dtype=_TORCH_DTYPE[self.buf_dtype],
                                      device=self.device) for _ in range(self.nranks)] for k, c in enumerate(caps)]
                 workspace = torch.empty(max(self.workspace_bytes, 1), dtype=torch.uint8, device=self.device)
+                # a step may run on any stream: what still uses this memory on the current one ends first
+                # (memory allocated under capture is the graph's own)
+                if not torch.cuda.is_current_stream_capturing():
+                    torch.cuda.current_stream(self.device).synchronize()
                 self._scratch = (sets, workspace, [[x.data_ptr() for x in bs] for bs in sets])
             return self._scratch
 
