@@ -409,6 +409,9 @@ def shape_of(full):
     if "tiles_kernel" in full:  # the vectors per lane: the last template argument
         m = re.search(r"tiles_kernel<[^>]*,\s*(\d+)>", full) or re.search(r"tiles_kernelI.*Li(\d+)EEEv", full)
         return f"tiles<{m.group(1)}>" if m else "tiles"
+    m = re.search(r"fold_(table|flat)_kernel(?:<[^>]*,\s*|I.*Li)(\d+)[>E]", full)
+    if m:
+        return f"{m.group(1)}, bursts of {m.group(2)}"
     m = re.search(r"(Policy|CopyCfg)<[^>]*>", full)
     if m:
         return m.group(0).replace(" ", "") + two
