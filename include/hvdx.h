@@ -332,7 +332,7 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
  *                             what its ring's chunks are cut from
  *   table                     host memory of `capacity` bytes, 16-byte aligned, or NULL for
  *                             a capacity (and a tile count) that is enough
- *   ntiles                    out: tiles in the table
+ *   ntiles, stretches         out: tiles in the table, and how many wavefronts a tile takes
  * Returns the table's bytes, or a negative HVDX_ERR_* (HVDX_ERR_WORKSPACE when capacity is too
  * small).  The table holds the tensors' addresses and belongs to these types and nranks.
  *
@@ -340,6 +340,7 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
  *   table      DEVICE copy of the table, 16-byte aligned (not checked: other contents make
  *              the kernel read or write outside the tensors)
  *   ntiles     <= HVDX_CYCLE_MAX_TILES
+ *   stretches  as hvdx_fuse_cycle_table gave it
  *   count      the buffers' elements, for the launch's shape and the timeline's record
  *   direct     1 when every buffer is a tensor reduced by itself: the timeline then says so
  * Errors: HVDX_ERR_INVALID, HVDX_ERR_UNSUPPORTED (binary16 tensors with a binary32 buffer, too
@@ -349,9 +350,9 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
 int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const int64_t* offset,
                               const int32_t* bucket_of, const int64_t* bucket_count, int ntensors, int nbuckets,
                               int tensor_dtype, int buf_dtype, int nranks, void* table, int64_t capacity,
-                              int64_t* ntiles);
-int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t count, int tensor_dtype, int buf_dtype,
-                    int nranks, int op, int direct, void* stream);
+                              int64_t* ntiles, int* stretches);
+int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int stretches, int64_t count, int tensor_dtype,
+                    int buf_dtype, int nranks, int op, int direct, void* stream);
 
 /*
  * hvdx_fuse_allreduce_small -- hvdx_fuse_allreduce for small fusion buffers: the same

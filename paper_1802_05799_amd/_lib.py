@@ -44,8 +44,8 @@ _SIGNATURES = {
     "hvdx_fuse_copy_tiles": (_i64, [_pi64, _p, _i, _i64, _i, _i, _i, _i, _p, _i64]),
     "hvdx_fuse_allreduce_tiled": (_i, [_p, _i, _i, _i, _i, _i, _i, _p]),
     "hvdx_fuse_tile_elems": (_i64, [_i, _i]),
-    "hvdx_fuse_cycle_table": (_i64, [_p, _p, _p, _p, _p, _i, _i, _i, _i, _i, _p, _i64, _pi64]),
-    "hvdx_fuse_cycle": (_i, [_p, _i, _i64, _i64, _i, _i, _i, _i, _i, _p]),
+    "hvdx_fuse_cycle_table": (_i64, [_p, _p, _p, _p, _p, _i, _i, _i, _i, _i, _p, _i64, _pi64, ctypes.POINTER(_i)]),
+    "hvdx_fuse_cycle": (_i, [_p, _i, _i64, _i, _i64, _i, _i, _i, _i, _i, _p]),
     "hvdx_ring_allreduce": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
     "hvdx_ring_allreduce_steps": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
     "hvdx_ring_allreduce_small": (_i, [_pp, _i, _i64, _i, _i, _p]),
@@ -295,27 +295,29 @@ def hvdx_fuse_allreduce_tiled(descs, tensor_dtype: int, buf_dtype: int, nranks: 
 
 def hvdx_fuse_cycle_table(tensors, numel, offset, bucket_of, bucket_count, tensor_dtype: int, buf_dtype: int,
                           nranks: int):
-    """(table's bytes, to be copied to the GPU, tiles in it); tensors: the nranks *
+    """(table's bytes, to be copied to the GPU, tiles in it, wavefronts per tile); tensors: the nranks *
     len(numel) device addresses, rank-major."""
     held = [array.array(code, values) for code, values in (("Q", tensors), ("q", numel), ("q", offset),
                                                            ("i", bucket_of), ("q", bucket_count))]
     args = (*(x.buffer_info()[0] for x in held), len(numel), len(bucket_count), tensor_dtype, buf_dtype, nranks)
-    ntiles = ctypes.c_int64()
-    size = lib.hvdx_fuse_cycle_table(*args, None, 0, ctypes.byref(ntiles))
+    ntiles, stretches = ctypes.c_int64(), ctypes.c_int()
+    out = ctypes.byref(ntiles), ctypes.byref(stretches)
+    size = lib.hvdx_fuse_cycle_table(*args, None, 0, *out)
     if size < 0:
         _check(int(size))
     table = bytearray(max(16, size))
     where = (ctypes.c_char * len(table)).from_buffer(table)
-    size = lib.hvdx_fuse_cycle_table(*args, where, size, ctypes.byref(ntiles))
+    size = lib.hvdx_fuse_cycle_table(*args, where, size, *out)
     if size < 0:
         _check(int(size))
     del where
-    return memoryview(table)[: max(16, size)], ntiles.value
+    return memoryview(table)[: max(16, size)], ntiles.value, stretches.value
 
 
-def hvdx_fuse_cycle(table_dev: int, ntensors: int, ntiles: int, count: int, tensor_dtype: int, buf_dtype: int,
-                    nranks: int, op: int, direct: bool, stream: int = 0) -> None:
-    _check(lib.hvdx_fuse_cycle(table_dev, ntensors, ntiles, count, tensor_dtype, buf_dtype, nranks, op, direct, stream))
+def hvdx_fuse_cycle(table_dev: int, ntensors: int, ntiles: int, stretches: int, count: int, tensor_dtype: int,
+                    buf_dtype: int, nranks: int, op: int, direct: bool, stream: int = 0) -> None:
+    _check(lib.hvdx_fuse_cycle(table_dev, ntensors, ntiles, stretches, count, tensor_dtype, buf_dtype, nranks, op, direct,
+                               stream))
 
 
 def hvdx_fuse_allreduce_small(tensors_dev: int, numel_dev: int, offset_dev: int, ntensors: int, tensor_dtype: int,

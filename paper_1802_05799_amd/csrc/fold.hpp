@@ -173,17 +173,71 @@ __device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, 
   for (int k = 0; k < n; ++k) ((Global<TT>)ptr(k))[e] = o;
 }
 
-// A wavefront's stretch of m (1 .. 64*V) elements.
+// Both at once, for a stretch with whole vectors (vecs >= 1, from element `head` on) and single
+// elements (rest >= 1: the `head` before the vectors, then those past them): one after the other
+// the second's loads would wait behind the first's stores (with that, and what precedes the first
+// 16-byte boundary in a wavefront of its own, Inception-V3's tensors reduced one by one on 16 ranks
+// 565 us, 510 so).  Lanes past the last vector or element
+// load that one too, and store nothing.
+template <typename TT, typename TB, int B, typename MT, typename Ptr>
+__device__ __forceinline__ void fold_edges(const Ptr& ptr, const RingArgs& a, int mode, int head, int vecs, int rest) {
+  using F = FoldTypes<TT, TB>;
+  const int n = a.n, lane = threadIdx.x;
+  const int i = lane < rest ? lane : rest - 1;
+  const unsigned voff = head * (unsigned)sizeof(TT) + (lane < vecs ? lane : vecs - 1) * 16u;
+  const unsigned eoff = (i < head ? i : vecs * F::V + i) * (unsigned)sizeof(TT);
+  auto vector = [&](TT* p) { return (Global<MT>)((Global<char>)p + voff); };
+  auto element = [&](TT* p) { return (Global<TT>)((Global<char>)p + eoff); };
+  typename F::acc s = (typename F::acc)((TB)-0.0f);
+  TB t = (TB)-0.0f;
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += B) {
+    typename F::vec x[B];
+    TT y[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      TT* p = ptr(k0 + j < n ? k0 + j : n - 1);
+      x[j] = __builtin_nontemporal_load(vector(p));
+      y[j] = *element(p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+      if (k0 + j < n) {
+        s = F::in(x[j]) + s;
+        t = (TB)y[j] + t;
+      }
+  }
+  const MT o = F::out(finish_vec<F::V>(s, a, mode));
+  const TT u = (TT)finish_one(t, a, mode);
+  if (lane < vecs) {
+#pragma unroll 4
+    for (int k = 0; k < n; ++k) __builtin_nontemporal_store(o, vector(ptr(k)));
+  }
+  if (lane < rest) {
+#pragma unroll 4
+    for (int k = 0; k < n; ++k) *element(ptr(k)) = u;
+  }
+}
+
+// A wavefront's stretch of m (1 .. 64*V) elements; aligned: its element `head` (< V) lies on a
+// 16-byte boundary of every rank (head is 0 if not).
 template <typename TT, typename TB, int B, typename Ptr>
-__device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int mode, int m, bool aligned) {
+__device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int mode, int m, bool aligned,
+                                             int head) {
   using F = FoldTypes<TT, TB>;
   const int lane = threadIdx.x;
-  const int vecs = m / F::V, rest = m - vecs * F::V;
-  if (lane < vecs) {
+  if (head > m) head = m;
+  const int vecs = (m - head) / F::V, rest = m - vecs * F::V;
+  if (vecs && rest) {
+    if (aligned) fold_edges<TT, TB, B, typename F::vec>(ptr, a, mode, head, vecs, rest);
+    else fold_edges<TT, TB, B, typename F::uvec>(ptr, a, mode, head, vecs, rest);
+  } else if (lane < vecs) {
     if (aligned) fold_vectors<TT, TB, B, typename F::vec>(ptr, a, mode);
     else fold_vectors<TT, TB, B, typename F::uvec>(ptr, a, mode);
+  } else if (lane < rest) {
+    fold_element<TT, TB>(ptr, a, mode, lane);
   }
-  if (lane < rest) fold_element<TT, TB>(ptr, a, mode, vecs * F::V + lane);
 }
 
 // Wavefronts per SIMD that the registers of a burst have to leave room for.

@@ -31,14 +31,14 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
     const int64_t e1 = (g + 1) * S < end ? (g + 1) * S : end;
     auto ptr = [&](int k) { return static_cast<TT*>(bufs.p[c + k]) + e0; };
     const bool al = aligned && e0 % FoldTypes<TT, TB>::V == 0;
-    fold_stretch<TT, TB, B>(ptr, a, mode, (int)(e1 - e0), al);
+    fold_stretch<TT, TB, B>(ptr, a, mode, (int)(e1 - e0), al, 0);
   }
 }
 
 // ---- the tensors of a table -------------------------------------------------------------
 //
-// kFoldParts blocks per tile of the table, one per 64*V elements of it; the table lists
-// every tensor's ranks twice over, too.  The table is read as constant memory: read as plain
+// One block per stretch of a tile of the table, which lists every
+// tensor's ranks twice over, too.  The table is read as constant memory: read as plain
 // memory, a store's pointer is a vector load behind the store before it, and a wavefront's N
 // stores go out one round trip apart (ResNet-50 on 8 ranks 265 us, 256 so; Inception-V3 on 16 510,
 // 486; VGG-16 on 32 6.20 ms, 5.98, in both the bursts and the wavefronts that suit it best).
@@ -49,25 +49,26 @@ template <typename TT, typename TB, int B>
 __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(FoldTable t, RingArgs a, int mode) {
   constexpr int S = kFoldLanes * FoldTypes<TT, TB>::V;
   const int64_t b = (int64_t)blockIdx.y * kFoldRow + blockIdx.x;
-  if (b >= t.ntiles * kFoldParts) return;
+  const bool wide = t.stretches != 1;
+  if (b >= t.ntiles * t.stretches) return;
   typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-  const i32x4 w = constant(reinterpret_cast<const i32x4*>(t.tiles))[b / kFoldParts];  // a FoldTile in one load
+  const i32x4 w = constant(reinterpret_cast<const i32x4*>(t.tiles))[wide ? b / kFoldWide : b];  // a FoldTile in one load
   const uint32_t bits = (uint32_t)w[3];
-  const int part = (int)(b % kFoldParts) * S;
+  const auto p = constant(t.ptrs) + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
+  const int part = wide ? (int)(b % kFoldWide) * S : 0;
   const int left = (int)(bits & 0xffff) - part;
   if (left <= 0) return;
-  const auto p = constant(t.ptrs) + (int64_t)w[2] * 2 * a.n + (bits >> 16 & 0xff);
   const int64_t li = ((int64_t)w[1] << 32 | (uint32_t)w[0]) + part;
   auto ptr = [&](int k) { return static_cast<TT*>(p[k]) + li; };
-  fold_stretch<TT, TB, B>(ptr, a, mode, left < S ? left : S, bits >> 24);
+  fold_stretch<TT, TB, B>(ptr, a, mode, left < S ? left : S, bits >> 24 & 1, (int)(bits >> 28));
 }
 
 // Whether to hold the wavefronts per CU down (fold_lds).  Not in a launch so short that filling the
 // chip is what counts (TB/s held and not: 8 ranks of 1M binary32 elements 4.69, 4.96; of 3M 5.46,
 // 5.44; of 6M 5.87, 5.45; 16 ranks of 0.3M 3.65, 4.06; of 1.5M 5.31, 5.13; 32 of 1.5M 5.36, 5.02; 4
-// of 3M 5.19, 5.30).  And not where more than 1/8 of the blocks have little or nothing to move
-// (short tensors, each cut into N chunks: Inception-V3's tensors reduced one by one on 16 ranks 605
-// us held, 580 not).
+// of 3M 5.19, 5.30).  And not where more than 1/8 of the blocks have little to move (short tensors,
+// each cut into N chunks; Inception-V3's tensors reduced one by one on 16 ranks have 4% more blocks
+// than whole stretches: 510 us held, 552 not; with 21% more it was 605 and 580).
 bool fold_holds(int64_t blocks, int64_t count, int nranks, int tensor_dtype) {
   const int64_t bytes = count * (tensor_dtype == HVDX_FLOAT16 ? 2 : 4);
   const int64_t filled = bytes / (kFoldLanes * 16);
@@ -115,7 +116,7 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
 
 hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int64_t count, int tensor_dtype, int buf_dtype,
                              int divmode, hipStream_t stream) {
-  const int64_t blocks = t.ntiles * kFoldParts;
+  const int64_t blocks = t.ntiles * t.stretches;
   const int64_t bx = blocks < kFoldRow ? blocks : kFoldRow;
   const dim3 grid((unsigned)bx, (unsigned)((blocks + bx - 1) / bx));
   const int burst = fold_burst(a.n);

@@ -969,9 +969,9 @@ int hvdx_fuse_allreduce_tiled(const hvdx_tiled_bucket* buckets, int nbuckets, in
 int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const int64_t* offset,
                               const int32_t* bucket_of, const int64_t* bucket_count, int ntensors, int nbuckets,
                               int tensor_dtype, int buf_dtype, int nranks, void* table, int64_t capacity,
-                              int64_t* ntiles) {
+                              int64_t* ntiles, int* stretches) {
   static const char* what = "hvdx_fuse_cycle_table";
-  if (ntensors < 0 || nbuckets < 0 || !ntiles ||
+  if (ntensors < 0 || nbuckets < 0 || !ntiles || !stretches ||
       (ntensors > 0 && (!tensors || !numel || !offset || !bucket_of || !bucket_count)))
     return fail(HVDX_ERR_INVALID, "%s: bad tensor table", what);
   const int es = elem_size(tensor_dtype);
@@ -1001,15 +1001,17 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
   hvdx::FoldTile* tiles = reinterpret_cast<hvdx::FoldTile*>(static_cast<char*>(table) + ptr_bytes);
   const int64_t room = table && capacity >= ptr_bytes ? (capacity - ptr_bytes) / (int64_t)sizeof(hvdx::FoldTile) : -1;
   const int64_t vec = hvdx::tile_vec_elems(tensor_dtype, buf_dtype);
-  const int64_t tile = hvdx::kFoldParts * 64 * vec;
-  int64_t n = 0;
-  if (!table) {  // an upper bound: a piece per chunk, its tiles, and what precedes its first 16-byte boundary
-    for (int t = 0; t < ntensors; ++t) {
-      const int64_t q = bucket_count[bucket_of[t]] / nranks;
-      const int64_t pieces = q ? std::min<int64_t>(nranks, numel[t] / q + 2) : std::min<int64_t>(nranks, numel[t]);
-      n += numel[t] / tile + 3 * pieces;
-    }
-    *ntiles = n;
+  int64_t n = 0, elements = 0, pieces = 0;
+  for (int t = 0; t < ntensors; ++t) {  // pieces: of the tensors' parts in each chunk, at most
+    const int64_t q = bucket_count[bucket_of[t]] / nranks;
+    pieces += q ? std::min<int64_t>(nranks, numel[t] / q + 2) : std::min<int64_t>(nranks, numel[t]);
+    elements += numel[t];
+  }
+  *stretches = hvdx::fold_stretches(elements / (64 * vec), pieces);
+  const bool narrow = *stretches == 1;
+  const int64_t tile = *stretches * 64 * vec;
+  if (!table) {  // an upper bound: every piece's tiles, and what precedes its first 16-byte boundary
+    *ntiles = n = elements / tile + 3 * pieces;
     return ptr_bytes + n * (int64_t)sizeof(hvdx::FoldTile);
   }
   for (int i = 0; i < hvdx::kFoldPad && room >= 0; ++i) ptrs[npointers - hvdx::kFoldPad + i] = nullptr;
@@ -1021,8 +1023,8 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
     const int64_t count = bucket_count[bucket_of[t]];
     const int64_t q = count / nranks, rem = count % nranks, big = rem * (q + 1);
     // Cut at chunk ends and where rank 0's addresses are multiples of a tile.  If the ranks' tensors lie
-    // alike to 16 bytes, a piece that starts off a 16-byte boundary ends at the next one, so that every
-    // other piece can be moved by aligned vectors; if not, none can.
+    // alike to 16 bytes, each can be moved by aligned vectors from its first 16-byte boundary on, where
+    // a wide tile has to begin (a narrow one names it); if not, none can.
     const int64_t at0 = (int64_t)(reinterpret_cast<uintptr_t>(tensors[t]) / es % tile);
     bool alike = true;
     for (int r = 1; r < nranks; ++r)
@@ -1032,12 +1034,13 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
       const int64_t stop = std::min(p1, (c + 1) * q + std::min<int64_t>(c + 1, rem));  // of this chunk's piece
       while (p < stop) {
         const int64_t at = at0 + (p - p0);
-        const bool off = at & (vec - 1);
-        const int64_t len = std::min(stop - p, alike && off ? vec - (at & (vec - 1)) : tile - (at & (tile - 1)));
+        const int64_t off = alike ? -at & (vec - 1) : 0;
+        const int64_t len = std::min(stop - p, off && !narrow ? off : tile - (at & (tile - 1)));
+        const bool aligned = alike && (narrow || !off);
         if (n < room) {
           tiles[n].li = p - p0;
           tiles[n].tensor = t;
-          tiles[n].bits = (uint32_t)len | (uint32_t)c << 16 | (uint32_t)(alike && !off) << 24;
+          tiles[n].bits = (uint32_t)len | (uint32_t)c << 16 | (uint32_t)aligned << 24 | (uint32_t)(aligned ? off : 0) << 28;
         }
         ++n;
         p += len;
@@ -1050,11 +1053,13 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
   return ptr_bytes + n * (int64_t)sizeof(hvdx::FoldTile);
 }
 
-int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t count, int tensor_dtype, int buf_dtype,
-                    int nranks, int op, int direct, void* stream) {
+int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int stretches, int64_t count, int tensor_dtype,
+                    int buf_dtype, int nranks, int op, int direct, void* stream) {
   static const char* what = "hvdx_fuse_cycle";
   if (ntensors < 0 || ntiles < 0 || (ntiles > 0 && (!table || ntensors == 0)))
     return fail(HVDX_ERR_INVALID, "%s: bad table", what);
+  if (stretches != 1 && stretches != hvdx::kFoldWide)
+    return fail(HVDX_ERR_INVALID, "%s: tiles of %d stretches", what, stretches);
   if (reinterpret_cast<uintptr_t>(table) & 15) return fail(HVDX_ERR_INVALID, "%s: table is not 16-byte aligned", what);
   if (!elem_size(tensor_dtype) || !elem_size(buf_dtype)) return fail(HVDX_ERR_INVALID, "%s: unknown dtype", what);
   if (tensor_dtype == HVDX_FLOAT16 && buf_dtype == HVDX_FLOAT32)
@@ -1075,6 +1080,7 @@ int hvdx_fuse_cycle(const void* table, int ntensors, int64_t ntiles, int64_t cou
   k.tiles = reinterpret_cast<const hvdx::FoldTile*>(static_cast<const char*>(table) +
                                                     hvdx::fold_pointers(ntensors, nranks) * (int64_t)sizeof(void*));
   k.ntiles = ntiles;
+  k.stretches = stretches;
   const hipError_t e = hvdx::launch_fold_table(k, ring_args(nranks, count, 0), count, tensor_dtype, buf_dtype,
                                                div_mode(op, nranks), st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "whole-cycle launch");

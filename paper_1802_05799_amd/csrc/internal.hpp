@@ -145,13 +145,20 @@ hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, 
 // the messages in registers.  Over flat rank buffers (a holds their partition):
 hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
                             bool aligned, hipStream_t stream);
-// ... and over the tensors of a table, where a tile is at most kFoldParts * 64 16-byte vectors
-// of one tensor in one ring chunk.
-constexpr int kFoldParts = 4;
+// ... and over the tensors of a table, where a tile is at most 64 16-byte vectors of one tensor in one
+// ring chunk, a wavefront's stretch, or kFoldWide times that.  Wide tiles leave blocks with nothing
+// to do at each piece's end, and need a tile of its own for what precedes a piece's first 16-byte
+// boundary; narrow ones are four times the table, which wavefronts on different XCDs each fetch from
+// memory.  So narrow where pieces are shorter than 64 stretches on average (us wide and narrow:
+// Inception-V3's tensors one by one on 16 ranks, 20 stretches to a piece, 565 and 510; in fusion
+// buffers, over 100, 486 and 491; ResNet-50 on 8 ranks 256 and 257).
+constexpr int kFoldWide = 4;
+inline int fold_stretches(int64_t stretches, int64_t pieces) { return stretches < 64 * pieces ? 1 : kFoldWide; }
 struct alignas(16) FoldTile {
   int64_t li;      // the tile's first element in its tensor
   int32_t tensor;
-  uint32_t bits;   // elements, the ring's first rank << 16, 16-byte aligned on every rank << 24
+  uint32_t bits;   // elements, the ring's first rank << 16, on every rank 16-byte aligned << 24 from
+                   // its first so many << 28 elements on
 };
 constexpr int kFoldPad = 16;  // pointers a burst may read past the last tensor's
 constexpr int64_t fold_pointers(int64_t ntensors, int nranks) { return ntensors * 2 * nranks + kFoldPad; }
@@ -159,6 +166,7 @@ struct FoldTable {
   void* const* ptrs;  // DEVICE [ntensors][2 * nranks]: each tensor's ranks, twice over, then kFoldPad zeros
   const FoldTile* tiles;  // DEVICE
   int64_t ntiles;
+  int stretches;  // of a tile: 1 or kFoldWide
 };
 hipError_t launch_fold_table(const FoldTable& t, const RingArgs& a, int64_t count, int tensor_dtype, int buf_dtype,
                              int divmode, hipStream_t stream);  // count: elements the tiles hold, about

@@ -215,13 +215,13 @@ class FusedAllreduce:
                     continue
                 bs = [self.buckets[i] for i in members]
                 ids = [t for b in bs for t in b.tensors]
-                table, ntiles = L.hvdx_fuse_cycle_table(
+                table, ntiles, stretches = L.hvdx_fuse_cycle_table(
                     [p[t] for p in ptrs for t in ids], [self.numel[t] for t in ids], [o for b in bs for o in b.offsets],
                     [k for k, b in enumerate(bs) for _ in b.tensors], [b.count for b in bs], self.dtype, self.buf_dtype, n)
                 dev_table = torch.frombuffer(table, dtype=torch.uint8).to(dev)
                 self._cycles.append(_Cycle(kind, tuple(members), dev_table, (
-                    dev_table.data_ptr(), len(ids), ntiles, sum(b.count for b in bs), self.dtype, self.buf_dtype, n,
-                    self.op, direct)))
+                    dev_table.data_ptr(), len(ids), ntiles, stretches, sum(b.count for b in bs), self.dtype, self.buf_dtype,
+                    n, self.op, direct)))
             self._cycles.sort(key=lambda c: c.members[0])  # in plan order
         elif self.tiled:
             for b in self.buckets:
