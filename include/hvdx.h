@@ -581,7 +581,7 @@ int hvdx_ring_chunk(int64_t count, int nranks, int c, int64_t* start, int64_t* l
 #define HVDX_KERNEL_ALLGATHER 2
 #define HVDX_KERNEL_UNPACK 3
 #define HVDX_KERNEL_ROUNDTRIP 4 /* one-rank compressed ring: round to binary16 and back */
-#define HVDX_KERNEL_BROADCAST 5 /* one step of hvdx_broadcast */
+#define HVDX_KERNEL_BROADCAST 5 /* a broadcast in one launch (step = -1), or one of its chain's steps */
 #define HVDX_KERNEL_RS_AG 6     /* last adding step and first replacing step in one launch */
 #define HVDX_KERNEL_FOLD 7      /* hvdx_fold_allreduce */
 #define HVDX_KERNEL_PACK_RS 8   /* copy-in with adding step 0 (step = 0) */

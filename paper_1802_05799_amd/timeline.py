@@ -49,9 +49,17 @@ def chunks_of_step(kind: int, step: int, rank: int, n: int):
 
 def broadcast_step_args(step: int, rank: int, root: int, n: int) -> dict:
     """What `rank` does in broadcast step `step`: rank root+k forwards chunk step-k to
-    its right neighbour (k = 0..N-2) and received chunk step-k+1 from its left one."""
+    its right neighbour (k = 0..N-2) and received chunk step-k+1 from its left one.  For
+    step -1, the whole chain in one launch: all N chunks, and the steps that carry them."""
     k = (rank - root) % n
     args = {}
+    if step < 0:
+        for way, end, first, there in (("send", "to", k, k <= n - 2), ("recv", "from", k - 1, k >= 1)):
+            if there:
+                args[f"{way} chunks"] = f"0-{n - 1}"
+                args[f"{way} steps"] = f"{first}-{first + n - 1}"
+                args[end] = (rank + (1 if way == "send" else -1)) % n
+        return args
     if k <= n - 2 and 0 <= step - k < n:
         args["send chunk"] = step - k
         args["to"] = (rank + 1) % n

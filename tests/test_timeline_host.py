@@ -50,3 +50,24 @@ def test_broadcast_labels_follow_the_oracle_chain():
                     if changed:
                         assert args.get("recv chunk") == changed[0] and len(changed) == 1
                 prev = cur
+
+
+def test_whole_broadcast_labels_cover_the_chain():
+    """A broadcast in one launch (step -1): every rank's track names the chunks it sends and
+    receives and in which steps, the union of its steps' labels."""
+    from paper_1802_05799_amd.timeline import broadcast_step_args
+
+    for n in (2, 3, 5, 8):
+        for root in range(n):
+            for r in range(n):
+                whole = broadcast_step_args(-1, r, root, n)
+                steps = [broadcast_step_args(s, r, root, n) for s in range(2 * n - 2)]
+                for way, end in (("send", "to"), ("recv", "from")):
+                    at = [(s, a[f"{way} chunk"]) for s, a in enumerate(steps) if f"{way} chunk" in a]
+                    if not at:
+                        assert end not in whole and f"{way} chunks" not in whole
+                        continue
+                    assert whole[end] == next(a[end] for a in steps if end in a)
+                    assert [j for _, j in at] == list(range(n)) and whole[f"{way} chunks"] == f"0-{n - 1}"
+                    assert whole[f"{way} steps"] == f"{at[0][0]}-{at[-1][0]}"
+                assert whole  # every rank of a chain of two or more sends or receives
