@@ -6,7 +6,11 @@ library brackets each kernel it launches with HIP events while a timeline
 records (hvdx_timeline_begin / hvdx_timeline_end); this module turns the records
 into Chrome trace JSON with one track per simulated rank, naming for every ring
 step the chunk the rank sends to its right neighbour and the chunk it receives
-from its left one, plus one track for the GPU kernels themselves.
+from its left one, plus one track for the GPU kernels themselves.  A record is a launch:
+an allreduce or broadcast that runs all its steps in one launch (the default) has one,
+which names every step's chunks but has no times for the single steps.  They have records
+of their own where they are launches of their own: FusedAllreduce(..., small_bucket_bytes=0),
+hvdx_ring_allreduce_steps, TensorBroadcast.step.
 
     with Timeline() as tl:
         allreduce()
@@ -45,6 +49,19 @@ def chunks_of_step(kind: int, step: int, rank: int, n: int):
     if kind == L.KERNEL_REDUCE_SCATTER:
         return (rank - step) % n, (rank - 1 - step) % n
     return (rank + 1 - step) % n, (rank - step) % n
+
+
+def whole_ring_args(rank: int, n: int) -> dict:
+    """What `rank` does in a ring that runs in one launch: the chunk it sends and receives in
+    step 0 of each half (every further step: one chunk lower, mod N), of each buffer's ring."""
+    if n < 2:
+        return {}
+    args = {"to": (rank + 1) % n, "from": (rank - 1) % n}
+    for phase, kind in (("adding", L.KERNEL_REDUCE_SCATTER), ("replacing", L.KERNEL_ALLGATHER)):
+        sent, recv = chunks_of_step(kind, 0, rank, n)
+        args[f"{phase} steps"] = f"0-{n - 2}, each one chunk lower (mod {n})"
+        args[f"{phase}: first chunk sent"], args[f"{phase}: first chunk received"] = sent, recv
+    return args
 
 
 def broadcast_step_args(step: int, rank: int, root: int, n: int) -> dict:
@@ -109,8 +126,7 @@ class Timeline:
                 if kind == L.KERNEL_BROADCAST:
                     args = broadcast_step_args(step, r, rec["root"], n)
                 if kind in (L.KERNEL_RING_SMALL, L.KERNEL_CYCLE_SMALL):
-                    args = {"steps": f"adding 0-{n - 2}, replacing 0-{n - 2}", "to": (r + 1) % n,
-                            "from": (r - 1) % n}
+                    args = whole_ring_args(r, n)
                 if kind == L.KERNEL_RS_AG:  # adding step N-2, then replacing step 0
                     args = {"send chunks": [(r + 2) % n, (r + 1) % n], "to": (r + 1) % n,
                             "recv chunks": [(r + 1) % n, r], "from": (r - 1) % n,

@@ -71,3 +71,20 @@ def test_whole_broadcast_labels_cover_the_chain():
                     assert [j for _, j in at] == list(range(n)) and whole[f"{way} chunks"] == f"0-{n - 1}"
                     assert whole[f"{way} steps"] == f"{at[0][0]}-{at[-1][0]}"
                 assert whole  # every rank of a chain of two or more sends or receives
+
+
+def test_one_launch_ring_labels_name_every_steps_chunks():
+    """A ring in one launch: a rank's track still says which chunk it sends and receives in
+    every step, as the first steps' chunks from which each further step counts down."""
+    from paper_1802_05799_amd.timeline import whole_ring_args
+
+    assert whole_ring_args(0, 1) == {}  # one rank sends nothing
+    for n in (2, 3, 5, 8, 17):
+        for r in range(n):
+            args = whole_ring_args(r, n)
+            assert args["to"] == (r + 1) % n and args["from"] == (r - 1) % n
+            for phase, kind in (("adding", hv._lib.KERNEL_REDUCE_SCATTER), ("replacing", hv._lib.KERNEL_ALLGATHER)):
+                assert args[f"{phase} steps"] == f"0-{n - 2}, each one chunk lower (mod {n})"
+                sent, recv = args[f"{phase}: first chunk sent"], args[f"{phase}: first chunk received"]
+                for s in range(n - 1):
+                    assert ((sent - s) % n, (recv - s) % n) == chunks_of_step(kind, s, r, n)
