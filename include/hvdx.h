@@ -510,24 +510,31 @@ int hvdx_broadcast_step(void* const* bufs, int nranks, int64_t nbytes, int root,
  *
  *   ptrs[nranks*ntensors]  DEVICE array of tensor pointers, rank-major (rank r's tensor t
  *                          at r*ntensors + t); the tensors must not overlap (not
- *                          checked: the table is in device memory); 16-byte aligned
- *                          copies move as vectors, others byte by byte
+ *                          checked: the table is in device memory).  The one launch
+ *                          moves 16 bytes an access whatever their alignment; a step does
+ *                          so for 16-byte aligned copies, others byte by byte
  *   nbytes[ntensors]       DEVICE array, bytes of each tensor (>= 0)
  *   voffset[ntensors]      DEVICE array, ascending multiples of 16 with
- *                          voffset[t] >= voffset[t-1] + nbytes[t-1].  (The one launch, not the
- *                          steps, takes any ascending starts that leave no 16-byte unit to two
- *                          tensors, and is fastest where they lie in a 4 KiB page as the ranks'
- *                          tensors do.)
+ *                          voffset[t] >= voffset[t-1] + nbytes[t-1]
  *   total_bytes            >= voffset[T-1] + nbytes[T-1]; 0 (or ntensors 0) is a no-op
  *   root                   0..nranks-1
  * hvdx_broadcast_layout (host) computes the densest layout: each tensor at the first
  * multiple of 16 at or after the previous one's end; total_bytes = the last one's end.
  * hvdx_broadcast_tensors_step runs step `step` (0 <= step < 2*nranks-2) alone.
+ * hvdx_broadcast_tensors_placed is the one launch over a space in which the tensors start
+ * anywhere: `start` ascending, none (nor an empty tensor's) in an aligned 16-byte unit of the
+ * space that holds bytes of an earlier tensor.  It is fastest where each tensor has pages of
+ * 4 KiB to itself and starts where its ranks' copies do in theirs: a wavefront then has one
+ * tensor, and whole cache lines.  extent_bytes >= the last one's end is the space's length,
+ * data_bytes (<= extent_bytes) the tensors' own bytes, for the launch's shape and the
+ * timeline's record (hvdx_broadcast_tensors takes total_bytes for both).
  * Errors: HVDX_ERR_INVALID (host-side arguments), HVDX_ERR_HIP.
  */
 int hvdx_broadcast_layout(const int64_t* nbytes, int ntensors, int64_t* voffset, int64_t* total_bytes);
 int hvdx_broadcast_tensors(const void* const* ptrs, const int64_t* nbytes, const int64_t* voffset, int ntensors,
                            int64_t total_bytes, int nranks, int root, void* stream);
+int hvdx_broadcast_tensors_placed(const void* const* ptrs, const int64_t* nbytes, const int64_t* start, int ntensors,
+                                  int64_t extent_bytes, int64_t data_bytes, int nranks, int root, void* stream);
 int hvdx_broadcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, const int64_t* voffset, int ntensors,
                                 int64_t total_bytes, int nranks, int root, int step, void* stream);
 

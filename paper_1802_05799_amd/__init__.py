@@ -41,6 +41,7 @@ from ._lib import (  # noqa: F401
     hvdx_broadcast_step,
     hvdx_broadcast_layout,
     hvdx_broadcast_tensors,
+    hvdx_broadcast_tensors_placed,
     hvdx_broadcast_tensors_step,
     hvdx_fold_allreduce,
     hvdx_fuse_ag_unpack,
@@ -83,10 +84,10 @@ _NBYTES = operator.attrgetter("nbytes")
 
 class TensorBroadcast:
     """Rank `root`'s tensors copied into every other rank's (paper sections 4 and 5:
-    consistent initial variables), every tensor of the list in one chain:
-    hvdx_broadcast_tensors runs the chain once for the whole list, in one launch; step()
-    runs one of its 2N-2 steps, over the tensors laid end to end at 16-byte aligned starts.  Bytes are copied, not
-    interpreted: tensor t must have the same byte count on every rank (any dtype), be
+    consistent initial variables), every tensor of the list in one chain: a call runs it
+    for the whole list, in one launch (hvdx_broadcast_tensors_placed); step() runs one of
+    its 2N-2 steps, over the tensors laid end to end at 16-byte aligned starts, `total`
+    bytes in all.  Bytes are copied, not interpreted: tensor t must have the same byte count on every rank (any dtype), be
     contiguous, on one GPU, and share memory with no other tensor.  The descriptor
     tables are uploaded once (asynchronously, from pinned memory); the tensors must stay
     allocated and in place."""
@@ -139,7 +140,7 @@ class TensorBroadcast:
         k = n * nt
         self._args = (self.tables.data_ptr(), self.tables.data_ptr() + 8 * k, self.tables.data_ptr() + 8 * (k + nt),
                       nt, self.total, n)
-        self._call_args = (*self._args[:2], self._args[2] + 8 * nt, nt, at, n)
+        self._call_args = (*self._args[:2], self._args[2] + 8 * nt, nt, at, self.total, n)
         self.tensors = per_rank  # keeps the tensors alive as long as the tables point at them
 
     def _stream(self, stream):
@@ -151,7 +152,7 @@ class TensorBroadcast:
         return stream
 
     def __call__(self, root: int = 0, stream: int | None = None) -> None:
-        hvdx_broadcast_tensors(*self._call_args, root, self._stream(stream))
+        hvdx_broadcast_tensors_placed(*self._call_args, root, self._stream(stream))
 
     def step(self, root: int, step: int, stream: int | None = None) -> None:
         """One chain step alone (hvdx_broadcast_tensors_step)."""

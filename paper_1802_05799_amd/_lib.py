@@ -63,6 +63,7 @@ _SIGNATURES = {
     "hvdx_broadcast_step": (_i, [_pp, _i, _i64, _i, _i, _p]),
     "hvdx_broadcast_layout": (_i, [_pi64, _i, _pi64, _pi64]),
     "hvdx_broadcast_tensors": (_i, [_p, _p, _p, _i, _i64, _i, _i, _p]),
+    "hvdx_broadcast_tensors_placed": (_i, [_p, _p, _p, _i, _i64, _i64, _i, _i, _p]),
     "hvdx_broadcast_tensors_step": (_i, [_p, _p, _p, _i, _i64, _i, _i, _i, _p]),
     "hvdx_fold_allreduce": (_i, [_pp, _i, _i64, _i, _i, _i, _p]),
     "hvdx_timeline_begin": (_i, [_i, _i]),
@@ -415,6 +416,12 @@ def hvdx_broadcast_layout(nbytes):
 def hvdx_broadcast_tensors(ptrs_dev: int, nbytes_dev: int, voffset_dev: int, ntensors: int, total_bytes: int,
                            nranks: int, root: int, stream: int = 0) -> None:
     _check(lib.hvdx_broadcast_tensors(ptrs_dev, nbytes_dev, voffset_dev, ntensors, total_bytes, nranks, root, stream))
+
+
+def hvdx_broadcast_tensors_placed(ptrs_dev: int, nbytes_dev: int, start_dev: int, ntensors: int, extent_bytes: int,
+                                  data_bytes: int, nranks: int, root: int, stream: int = 0) -> None:
+    _check(lib.hvdx_broadcast_tensors_placed(ptrs_dev, nbytes_dev, start_dev, ntensors, extent_bytes, data_bytes, nranks,
+                                             root, stream))
 
 
 def hvdx_broadcast_tensors_step(ptrs_dev: int, nbytes_dev: int, voffset_dev: int, ntensors: int, total_bytes: int,

@@ -1602,8 +1602,8 @@ void bcast_tensors_launch(const BcastTensorsArgs& a, unsigned lds, hipStream_t s
 }
 }  // namespace
 
-hipError_t launch_bcast_tensors(const BcastTensorsArgs& a, hipStream_t stream) {
-  const BcastShape s = bcast_shape(a.n, a.total);
+hipError_t launch_bcast_tensors(const BcastTensorsArgs& a, int64_t data, hipStream_t stream) {
+  const BcastShape s = bcast_shape(a.n, data);
   if (s.units == 4) bcast_tensors_launch<4>(a, s.lds, stream);
   else if (s.units == 2) bcast_tensors_launch<2>(a, s.lds, stream);
   else bcast_tensors_launch<1>(a, s.lds, stream);

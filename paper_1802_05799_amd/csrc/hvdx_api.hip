@@ -1215,9 +1215,10 @@ static int check_bcast_tensors(const void* const* ptrs, const int64_t* nbytes, c
   return HVDX_OK;
 }
 
-// Chain step `step`, or, for step < 0, the whole broadcast in one launch.
+// Chain step `step`, or, for step < 0, the whole broadcast in one launch.  `data` is what a record
+// counts and the one launch's shape goes by: the tensors' bytes without a sparse space's gaps.
 static int bcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, const int64_t* voffset, int ntensors,
-                              int64_t total_bytes, int nranks, int root, int step, hipStream_t st) {
+                              int64_t total_bytes, int64_t data, int nranks, int root, int step, hipStream_t st) {
   hvdx::BcastTensorsArgs a{};
   a.ptrs = ptrs;
   a.nbytes = nbytes;
@@ -1230,9 +1231,9 @@ static int bcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, co
   const int64_t units = (total_bytes + 15) / 16;
   a.q = units / nranks;
   a.rem = units % nranks;
-  TimedLaunch timed(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, total_bytes, st, root);
-  TimedLaunch timed_phase(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, total_bytes, st, root, true);
-  const hipError_t e = step < 0 ? hvdx::launch_bcast_tensors(a, st) : hvdx::launch_bcast_tensors_step(a, st);
+  TimedLaunch timed(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, data, st, root);
+  TimedLaunch timed_phase(HVDX_KERNEL_BROADCAST, step, nranks, -1, HVDX_COMPRESS_NONE, data, st, root, true);
+  const hipError_t e = step < 0 ? hvdx::launch_bcast_tensors(a, data, st) : hvdx::launch_bcast_tensors_step(a, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "tensor broadcast step launch");
 }
 
@@ -1244,7 +1245,7 @@ int hvdx_broadcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, 
   if (step < 0 || step > 2 * nranks - 3)
     return fail(HVDX_ERR_INVALID, "hvdx_broadcast_tensors_step: step %d outside 0..%d", step, 2 * nranks - 3);
   if (total_bytes == 0 || ntensors == 0) return HVDX_OK;
-  return bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, step,
+  return bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, total_bytes, nranks, root, step,
                             static_cast<hipStream_t>(stream));
 }
 
@@ -1253,7 +1254,20 @@ int hvdx_broadcast_tensors(const void* const* ptrs, const int64_t* nbytes, const
   int rc = check_bcast_tensors(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, "hvdx_broadcast_tensors");
   if (rc) return rc;
   if (total_bytes == 0 || ntensors == 0 || nranks == 1) return HVDX_OK;
-  return bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, nranks, root, -1,
+  return bcast_tensors_step(ptrs, nbytes, voffset, ntensors, total_bytes, total_bytes, nranks, root, -1,
+                            static_cast<hipStream_t>(stream));
+}
+
+int hvdx_broadcast_tensors_placed(const void* const* ptrs, const int64_t* nbytes, const int64_t* start, int ntensors,
+                                  int64_t extent_bytes, int64_t data_bytes, int nranks, int root, void* stream) {
+  static const char* what = "hvdx_broadcast_tensors_placed";
+  int rc = check_bcast_tensors(ptrs, nbytes, start, ntensors, extent_bytes, nranks, root, what);
+  if (rc) return rc;
+  if (data_bytes < 0 || data_bytes > extent_bytes)
+    return fail(HVDX_ERR_INVALID, "%s: %lld bytes in an extent of %lld", what, (long long)data_bytes,
+                (long long)extent_bytes);
+  if (extent_bytes == 0 || ntensors == 0 || nranks == 1) return HVDX_OK;
+  return bcast_tensors_step(ptrs, nbytes, start, ntensors, extent_bytes, data_bytes, nranks, root, -1,
                             static_cast<hipStream_t>(stream));
 }
 

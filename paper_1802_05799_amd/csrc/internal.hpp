@@ -209,8 +209,9 @@ struct BcastTensorsArgs {
   int64_t q, rem;           // 16-byte units per chunk: q, the first rem chunks one more
 };
 hipError_t launch_bcast_tensors_step(const BcastTensorsArgs& a, hipStream_t stream);
-// The whole broadcast in one launch (a.step is not used).
-hipError_t launch_bcast_tensors(const BcastTensorsArgs& a, hipStream_t stream);
+// The whole broadcast in one launch (a.step is not used); data: the tensors' bytes, about, which
+// decide the launch's shape (the space may be far longer than they are).
+hipError_t launch_bcast_tensors(const BcastTensorsArgs& a, int64_t data, hipStream_t stream);
 
 // Launchers (fusion_kernels.hip).  With `ring` (nranks >= 3), the copy-in also does
 // the ring's adding step 0 (and with `skip_sender` leaves out each chunk's sender's

@@ -192,6 +192,18 @@ def test_broadcast_argument_errors():
     assert status_of(st, bufs(1, 64), 1, 64, 0, 0) == hv.ERR_INVALID  # no steps with one rank
 
 
+def test_placed_broadcast_argument_errors():
+    pl = hv.hvdx_broadcast_tensors_placed
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, 8192, 100, 3, 3) == hv.ERR_INVALID  # root out of range
+    assert status_of(pl, FAKE, FAKE, 0, 2, 8192, 100, 3, 0) == hv.ERR_INVALID  # a table missing
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, -1, 0, 3, 0) == hv.ERR_INVALID
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, 8192, -1, 3, 0) == hv.ERR_INVALID
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, 8192, 8193, 3, 0) == hv.ERR_INVALID  # more data than space
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, 8192, 100, 129, 0) == hv.ERR_INVALID
+    assert status_of(pl, FAKE, FAKE, FAKE, 2, 8192, 100, 1, 0) == hv.OK  # one rank: nothing to copy
+    assert status_of(pl, 0, 0, 0, 0, 0, 0, 3, 0) == hv.OK
+
+
 def test_fold_argument_errors():
     fo = hv.hvdx_fold_allreduce
     assert status_of(fo, bufs(2, 8), 0, 8, hv.FLOAT32, hv.SUM) == hv.ERR_INVALID

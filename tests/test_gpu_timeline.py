@@ -121,3 +121,23 @@ def test_per_phase_records(mode):
             want.append((3, -1, 1))
     assert any(not b.direct for b in ar.buckets) and any(b.direct for b in ar.buckets)
     assert got == want
+
+
+def test_broadcasts_record_the_tensors_bytes():
+    """A list's broadcast in one launch records step -1 and the same bytes as the chain's steps,
+    not its virtual space, which keeps each tensor in pages of its own."""
+    say("timeline of broadcasts")
+    per_rank = tensors(4, [7, 4000, 0, 100, 1, 3])
+    tb = hv.TensorBroadcast(per_rank)
+    flat = tensors(3, [1001])
+    with hv.Timeline(capacity=100) as tl:
+        tb(1)
+        tb.step(1, 0)
+        hv.hvdx_broadcast([x.data_ptr() for (x,) in flat], 3, 4004, 2, torch.cuda.current_stream().cuda_stream)
+    got = [(r["kind"], r["step"], r["root"], r["count"]) for r in tl.records]
+    data = sum(x.nbytes for x in per_rank[0])
+    assert data <= tb.total < data + 16 * len(per_rank[0])
+    code = hv._lib.KERNEL_BROADCAST
+    assert got == [(code, -1, 1, tb.total), (code, 0, 1, tb.total), (code, -1, 2, 4004)]
+    tracks = [e for e in tl.chrome_trace()["traceEvents"] if e["ph"] == "X" and e["tid"] > 0]
+    assert all("to" in e["args"] or "from" in e["args"] for e in tracks[:4])  # the whole chain's ranks
