@@ -1316,7 +1316,7 @@ __global__ __launch_bounds__(64) void bcast_tensors_kernel(BcastTensorsArgs a) {
             if (e[u] >= 0) __builtin_nontemporal_store((b32x4u)x[u], (Global<b32x4u>)(d[i] + e[u]));
         }
       }
-    } else if (at < len) {  // a tensor of less than a unit
+    } else if (len > 0 && at < len) {  // a tensor of less than a unit (an empty one's pointers may be NULL)
       unsigned char x[V];
 #pragma unroll
       for (int k = 0; k < V; ++k) x[k] = src[k < len ? k : 0];

@@ -31,6 +31,8 @@ class Knobs:
     fused_own_from_buffer: bool = False  # the fused step reads the owner's value from its buffer (False)
     xcd_shift: int = 0  # added to a block's XCD in tile_block() (0)
     bucket_end_shift: int = 0  # added to each bucket's first launch tile in ring_bucket() (0)
+    empty_is_read: bool = False  # the one-launch broadcast reads an empty tensor's first byte (False)
+    clamp_tail: bool = True  # a one-launch broadcast's short last unit is the last 16 bytes (True)
 
 
 K = Knobs()
@@ -541,6 +543,73 @@ def bcast_tensors_step(n, nbytes, root, step, k=K):
                 stop = min(p + 16, lay.end[t], p1)
                 add(w[dst][t], np.arange(p - starts[t], stop - starts[t]))
                 add(rd[src][t], np.arange(p - starts[t], stop - starts[t]), "read")
+    return w, rd
+
+
+# ---- a tensor list's broadcast in one launch (bcast_tensors_kernel) -----------------------
+def find_span_wave(start, p):
+    """find_span_wave(): (last tensor starting at or before p, its start, the next one's), by
+    rounds of 63 probes."""
+    n, lo, left = len(start), 0, len(start)
+    far = (1 << 63) - 1
+    while left > 63:
+        stride = (left + 62) // 63
+        c = sum(1 for lane in range(64) if lane * stride < left
+                and start[lo + lane * stride if lo + lane * stride < n else 0] <= p)
+        if c == 0:
+            break
+        lo += (c - 1) * stride
+        left = min(left - (c - 1) * stride, stride)
+    v = [start[lo + lane] if lo + lane < n else far for lane in range(64)]
+    c = sum(1 for x in v if x <= p)
+    return lo + c - 1, v[c - 1] if c else 0, v[c if c < 63 else 63]
+
+
+def unit_bytes(at, length, k=K):
+    """The 16 bytes a lane moves for the unit that starts at byte `at` of `length` (>= 16), if any."""
+    if at >= length or at <= -16:
+        return None
+    e = 0 if at < 0 else length - 16 if at + 16 > length and k.clamp_tail else at
+    return np.arange(e, e + 16)
+
+
+def bcast_tensors_whole(nbytes, start, extent, U, k=K):
+    """bcast_tensors_kernel: per tensor, how often each byte is stored to a receiving rank (its
+    loads from the root are the same bytes; a tensor shorter than a unit loads byte 0 for the
+    missing ones)."""
+    w = [np.zeros(b, np.int64) for b in nbytes]
+    rd = [np.zeros(b, np.int64) for b in nbytes]
+
+    def copy(t, p, units):
+        at, length = p - start[t], nbytes[t]
+        if length >= 16:
+            for u in range(units):
+                b = unit_bytes(at + u * 64 * 16, length, k)
+                if b is not None:
+                    add(rd[t], b, "read")
+                    add(w[t], b)
+        elif at < length and (length > 0 or k.empty_is_read):
+            add(rd[t], [e if e < length else 0 for e in range(16)], "read")
+            add(w[t], np.arange(length))
+
+    tile = 64 * U * 16
+    for b in range(-(-extent // tile)):
+        p0, p1 = b * tile, min((b + 1) * tile, extent)
+        last = (p1 - 1) | 15
+        t0, _, nxt = find_span_wave(start, p0 + 15)
+        if nxt > last:
+            for lane in range(64 if t0 >= 0 else 0):
+                copy(t0, p0 + (lane + k.lane_shift) * 16, U)
+            continue
+        t1, _, _ = find_span_wave(start, last)
+        for u in range(U):
+            for lane in range(64):
+                p = p0 + (u * 64 + lane + k.lane_shift) * 16
+                if p >= p1:
+                    break
+                t = int(np.searchsorted(start[max(t0, 0) : t1 + 1], p + 15, side="right")) - 1 + max(t0, 0)
+                if t >= max(t0, 0):
+                    copy(t, p, 1)
     return w, rd
 
 

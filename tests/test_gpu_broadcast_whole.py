@@ -83,3 +83,26 @@ def test_large_lists_take_every_shape(n):
     torch.cuda.synchronize()
     assert all(torch.equal(x, w) for row in rows for x, w in zip(row, want))
     assert all(torch.equal(x, want_flat) for x in flat)
+
+
+def test_placed_with_empty_tensors_between():
+    """hvdx_broadcast_tensors_placed with starts that are no multiples of 16, an empty tensor's
+    (whose pointers are NULL) among them."""
+    n, root = 3, 1
+    sizes, starts = [20, 0, 100, 0], [0, 40, 4104, 4208]
+    say("placed broadcast with empty tensors")
+    rng = np.random.default_rng(810)
+    x = [[rng.integers(0, 256, size=s, dtype=np.uint8) for s in sizes] for _ in range(n)]
+    bases, views = tensor_views(x, sizes, [0, 0, 8, 0])
+    ptrs = [v.data_ptr() if s else 0 for row in views for v, s in zip(row, sizes)]
+    table = torch.tensor(ptrs + sizes + starts, dtype=torch.int64, device="cuda")
+    at = table.data_ptr()
+    hv.hvdx_broadcast_tensors_placed(at, at + 8 * n * 4, at + 8 * (n + 1) * 4, 4, 4208, 120, n, root,
+                                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = host_state(views)
+    assert all(np.array_equal(got[r][t], x[root][t]) for r in range(n) for t in range(4))
+    for row, szs in zip(bases, [sizes] * n):
+        for b, s, off in zip(row, szs, [0, 0, 8, 0]):
+            g = b.cpu().numpy()
+            assert np.all(g[: 48 + off] == 0x5A) and np.all(g[48 + off + s :] == 0x5A)

@@ -222,6 +222,68 @@ def test_tensor_broadcast_steps():
             assert np.array_equal(total[t], want), t
 
 
+def dense_starts(sizes):
+    starts, end = [], 0
+    for b in sizes:
+        starts.append(-(-end // 16) * 16)
+        end = starts[-1] + b
+    return starts, end
+
+
+def paged_starts(sizes, addresses):
+    """TensorBroadcast's space: every tensor in pages of its own, where rank 0's address lies in one."""
+    starts, end = [], 0
+    for b, p in zip(sizes, addresses):
+        starts.append(-(-end // 4096) * 4096 + p % 4096)
+        end = starts[-1] + b
+    return starts, end
+
+
+def check_whole_list(sizes, starts, extent, U, **kw):
+    w, rd = W.bcast_tensors_whole(sizes, starts, extent, U, **kw)
+    assert all((x >= 1).all() for x in w)  # neighbours may store the same bytes, never others
+    assert all((r[x > 0] >= 1).all() for x, r in zip(w, rd))
+
+
+def test_tensor_search_of_a_wavefront():
+    rng = np.random.default_rng(40)
+    for n in (1, 2, 62, 63, 64, 65, 700, 63 * 63, 63 * 63 + 1, 6000):
+        start = np.cumsum(rng.integers(0, 4, size=n)).astype(np.int64).tolist()
+        for p in [-1, 0, start[0], start[-1], start[-1] + 9] + rng.integers(0, start[-1] + 1, size=12).tolist():
+            t = int(np.searchsorted(start, p, side="right")) - 1
+            got = W.find_span_wave(start, p)
+            assert got[0] == t and got[2] == (start[t + 1] if t + 1 < n else (1 << 63) - 1)
+            assert t < 0 or got[1] == start[t]
+
+
+@pytest.mark.parametrize("U", [1, 2, 4])
+def test_whole_tensor_broadcast_stores_every_byte(U):
+    rng = np.random.default_rng(41)
+    lists = [[1], [0, 1, 2, 15, 16, 17, 3, 0, 31, 33, 1], [1023, 1, 1024, 4097, 2048, 16, 4095, 8200],
+             rng.integers(0, 41, size=200).tolist()]
+    for sizes in lists:
+        check_whole_list(sizes, *dense_starts(sizes), U)
+        for anywhere in (False, True):  # an empty tensor's address is 0
+            at = [int(rng.integers(0, 1 << 20)) if b and anywhere else 256 * i if b else 0 for i, b in enumerate(sizes)]
+            check_whole_list(sizes, *paged_starts(sizes, at), U)
+
+
+def test_whole_tensor_broadcast_leaves_empty_tensors_alone():
+    """An empty tensor may start anywhere in the one launch's space, and its pointers may be NULL:
+    nothing of it is read.  (Read where its start is not a multiple of 16, it was.)"""
+    sizes, starts = [20, 0, 100, 0], [0, 40, 4104, 4208]
+    check_whole_list(sizes, starts, 4208, 2)
+    with pytest.raises(IndexError):
+        check_whole_list(sizes, starts, 4208, 2, k=W.Knobs(empty_is_read=True))
+
+
+@pytest.mark.parametrize("knobs", [W.Knobs(lane_shift=1), W.Knobs(clamp_tail=False)], ids=["lane", "tail"])
+def test_planted_whole_broadcast_mistakes_are_caught(knobs):
+    sizes = [1023, 1, 1024, 4097]
+    with pytest.raises((AssertionError, IndexError)):
+        check_whole_list(sizes, *dense_starts(sizes), 2, k=knobs)
+
+
 def test_buffers_past_2_to_31_elements():
     """The 2^31 + 4099-element rank buffers of the large GPU tests: grid sizes stay in
     range, and the vector spans of the first, middle and last blocks of each launch
