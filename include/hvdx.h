@@ -410,6 +410,7 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
  * hvdx_ring_allreduce runs all of it in one launch: an element's ring never involves another
  * element, so a lane takes its elements through every step, the messages in registers (2N
  * elements moved per element; the workspace is checked but not used).
+ * hvdx_ring_allreduce_whole is that without a workspace argument, compressed or not.
  * hvdx_ring_allreduce_steps runs a launch per step, the messages through the buffers (and the
  * workspace), for tracing: every step then has its record in a timeline.  (Adding step N-2
  * and replacing step 0 run as one kernel there; the buffers end the same.)  Same bits.
@@ -417,6 +418,8 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
  */
 int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                         void* workspace, size_t workspace_bytes, void* stream);
+int hvdx_ring_allreduce_whole(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+                              void* stream);
 int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                               void* workspace, size_t workspace_bytes, void* stream);
 
@@ -593,7 +596,7 @@ int hvdx_ring_chunk(int64_t count, int nranks, int c, int64_t* start, int64_t* l
 #define HVDX_KERNEL_FOLD 7      /* hvdx_fold_allreduce */
 #define HVDX_KERNEL_PACK_RS 8   /* copy-in with adding step 0 (step = 0) */
 #define HVDX_KERNEL_AG_UNPACK 9 /* replacing step N-2 with copy-out (step = N-2) */
-#define HVDX_KERNEL_RING_SMALL 10  /* hvdx_ring_allreduce(_small, _noalloc): every step in one launch */
+#define HVDX_KERNEL_RING_SMALL 10  /* hvdx_ring_allreduce(_whole, _small, _noalloc): every step in one launch */
 #define HVDX_KERNEL_CYCLE_SMALL 11 /* hvdx_fuse_cycle, hvdx_fuse_allreduce_small: whole cycles in one launch */
 
 typedef struct hvdx_trace_record {

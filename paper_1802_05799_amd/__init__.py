@@ -65,6 +65,7 @@ from ._lib import (  # noqa: F401
     hvdx_ring_allreduce_small,
     hvdx_ring_allreduce_noalloc,
     hvdx_ring_allreduce_steps,
+    hvdx_ring_allreduce_whole,
     hvdx_ring_noalloc_max_bytes,
     hvdx_ring_chunk,
     hvdx_ring_reduce_scatter,

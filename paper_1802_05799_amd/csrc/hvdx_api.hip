@@ -576,6 +576,21 @@ int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
 }
 
+int hvdx_ring_allreduce_whole(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+                              void* stream) {
+  static const char* what = "hvdx_ring_allreduce_whole";
+  if (compress != HVDX_COMPRESS_NONE && compress != HVDX_COMPRESS_FP16)
+    return fail(HVDX_ERR_INVALID, "%s: unknown compression %d", what, compress);
+  if (compress == HVDX_COMPRESS_FP16 && dtype != HVDX_FLOAT32)
+    return fail(HVDX_ERR_INVALID, "%s: fp16 compression needs float32 buffers", what);
+  int rc = check_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, nullptr, 0, what);
+  if (rc) return rc;
+  if (count == 0) return HVDX_OK;
+  if (nranks == 1)
+    return run_phase(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, nullptr, 0, stream, what);
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
+}
+
 int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                               void* workspace, size_t workspace_bytes, void* stream) {
   static const char* what = "hvdx_ring_allreduce_steps";

@@ -66,11 +66,12 @@ class Bucket:
 
 @dataclass
 class _Cycle:
-    """One hvdx_fuse_cycle launch: its buckets, their device table and the call's arguments."""
+    """One launch of whole rings: its buckets, the call and its arguments (all but the stream)."""
     kind: str  # "cycle_small" (fusion buffers) or "ring_small" (tensors reduced by themselves)
     members: tuple
-    table: torch.Tensor
+    call: object
     args: tuple
+    table: torch.Tensor | None = None  # hvdx_fuse_cycle's, on the GPU
 
 
 def _check_disjoint(tensors) -> None:
@@ -209,8 +210,15 @@ class FusedAllreduce:
         self._cycles = None
         if whole:
             self._cycles = []
-            for direct, kind in ((False, "cycle_small"), (True, "ring_small")):
-                members = [i for i, b in enumerate(self.buckets) if b.direct == direct and b.count > 0]
+            fused = [i for i, b in enumerate(self.buckets) if not b.direct and b.count > 0]
+            direct = [i for i, b in enumerate(self.buckets) if b.direct and b.count > 0]
+            alone = self._launched_alone(direct, ptrs)
+            for i in alone:
+                b = self.buckets[i]
+                bufs, _ = L._ptr_array([p[b.tensors[0]] for p in ptrs])
+                self._cycles.append(_Cycle("ring_small", (i,), L.hvdx_ring_allreduce_whole,
+                                           (bufs, n, b.count, self.dtype, self.op, self.compress)))
+            for members, kind in ((fused, "cycle_small"), ([i for i in direct if i not in alone], "ring_small")):
                 if not members:
                     continue
                 bs = [self.buckets[i] for i in members]
@@ -219,9 +227,9 @@ class FusedAllreduce:
                     [p[t] for p in ptrs for t in ids], [self.numel[t] for t in ids], [o for b in bs for o in b.offsets],
                     [k for k, b in enumerate(bs) for _ in b.tensors], [b.count for b in bs], self.dtype, self.buf_dtype, n)
                 dev_table = torch.frombuffer(table, dtype=torch.uint8).to(dev)
-                self._cycles.append(_Cycle(kind, tuple(members), dev_table, (
+                self._cycles.append(_Cycle(kind, tuple(members), L.hvdx_fuse_cycle, (
                     dev_table.data_ptr(), len(ids), ntiles, stretches, sum(b.count for b in bs), self.dtype, self.buf_dtype,
-                    n, self.op, direct)))
+                    n, self.op, kind == "ring_small"), dev_table))
             self._cycles.sort(key=lambda c: c.members[0])  # in plan order
         elif self.tiled:
             for b in self.buckets:
@@ -235,6 +243,22 @@ class FusedAllreduce:
                     tabs += [host.to(dev), k]
                 b.tiles = tuple(tabs)
         _timeline.start_from_env()
+
+    def _launched_alone(self, direct, ptrs):
+        """Which of the direct buckets run in a launch of their own, over flat rank buffers, and need
+        no entries in a table, whose cutting and upload count in a call made once (allreduce_ of
+        one tensor of 411 MB on 2 ranks: 651 us with a table, 284 us so; on 3: 766, 398; on 8:
+        1415, 1046; repeated calls take the same time).  Those above 64 MiB a rank, whose own
+        launch costs next to nothing, and a last one left.  Not where a rank's start is off a
+        16-byte boundary, which only the table's tiles make up for, and not with more ranks, whose
+        rings take long enough for a table not to count."""
+        if self.nranks > 8:
+            return []
+        aligned = [i for i in direct if all(p[self.buckets[i].tensors[0]] % 16 == 0 for p in ptrs)]
+        size = _TORCH_DTYPE[self.dtype].itemsize
+        alone = [i for i in aligned if self.buckets[i].count * size > L.DEFAULT_FUSION_THRESHOLD]
+        rest = [i for i in direct if i not in alone]
+        return alone + rest if len(rest) == 1 and rest[0] in aligned else alone
 
     # ---- memory of the per-step path: allocated with the object, or, where calls do not need it, when
     # one of the steps below is first asked for ----------------------------------------------------
@@ -416,7 +440,7 @@ class FusedAllreduce:
             stream = current_stream(self.device)
         if self._cycles is not None:
             for c in self._cycles:
-                L.hvdx_fuse_cycle(*c.args, stream)
+                c.call(*c.args, stream)
             return
         for i, b in enumerate(self.buckets):
             if b.group and b.slot == 0:

@@ -130,6 +130,21 @@ def test_ring_argument_errors():
     assert "overlap" in hv.hvdx_last_error() or hv.hvdx_last_error()
 
 
+def test_whole_ring_argument_errors():
+    wr = hv.hvdx_ring_allreduce_whole
+    assert status_of(wr, bufs(2, 8), 0, 8, hv.FLOAT32, hv.SUM) == hv.ERR_INVALID
+    assert status_of(wr, bufs(2, 8), 2, -1, hv.FLOAT32, hv.SUM) == hv.ERR_INVALID
+    assert status_of(wr, bufs(2, 8), 2, 8, 7, hv.SUM) == hv.ERR_INVALID  # dtype
+    assert status_of(wr, bufs(2, 8), 2, 8, hv.FLOAT32, 9) == hv.ERR_INVALID  # op
+    assert status_of(wr, bufs(2, 8), 2, 8, hv.FLOAT32, hv.SUM, 5) == hv.ERR_INVALID  # compression
+    assert status_of(wr, bufs(2, 8), 2, 8, hv.FLOAT16, hv.SUM, hv.COMPRESS_FP16) == hv.ERR_INVALID
+    assert status_of(wr, [FAKE, 0], 2, 8, hv.FLOAT32, hv.SUM) == hv.ERR_INVALID
+    assert status_of(wr, [FAKE, FAKE + 2], 2, 8, hv.FLOAT32, hv.SUM) == hv.ERR_INVALID
+    assert status_of(wr, [FAKE, FAKE + 16], 2, 8, hv.FLOAT32, hv.SUM, hv.COMPRESS_FP16) == hv.ERR_ALIAS
+    assert status_of(wr, bufs(4, 0), 4, 0, hv.FLOAT32, hv.AVERAGE, hv.COMPRESS_FP16) == hv.OK
+    assert status_of(wr, bufs(1, 8), 1, 8, hv.FLOAT32, hv.AVERAGE) == hv.OK  # one rank: no messages
+
+
 def test_fusion_argument_errors():
     pk, up = hv.hvdx_fuse_pack, hv.hvdx_fuse_unpack
     b = bufs(2, 64)

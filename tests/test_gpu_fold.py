@@ -8,7 +8,7 @@ import torch
 
 import paper_1802_05799_amd as hv
 from _gpu import NP_TO_HV, OPS, assert_bits_equal, from_gpu_rows, say, to_gpu_rows
-from oracle import allreduce
+from oracle import allreduce, native
 from test_gpu_ring import inputs, oracle_ring
 
 pytestmark = pytest.mark.gpu
@@ -125,3 +125,37 @@ def test_steps_of_a_one_launch_object():
             for r in range(n):
                 for t in range(len(numel)):
                     assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
+
+
+ALONE_CASES = [
+    # (numel, ranks, threshold, binary16 tensors, compress, elements off a 16-byte start, launches without a table)
+    ([17_000_001], 2, 64 << 20, False, False, 0, [0]),  # above 64 MiB a rank
+    ([5, 17_000_000, 3001], 3, 1 << 20, False, True, 0, [1]),  # compressed; the others in a fusion buffer
+    ([700, 900, 1000], 5, 2000, False, False, 0, []),  # three direct tensors share a table
+    ([300, 900, 200], 5, 2000, False, False, 0, [1]),  # the only direct one
+    ([900, 200], 4, 1000, True, False, 0, [0]),
+    ([900], 4, 0, False, False, 1, []),  # off a 16-byte start: only a table's tiles make up for it
+    ([900], 9, 0, False, False, 0, []),  # more than 8 ranks: a table does not count
+]
+
+
+@pytest.mark.parametrize("case", range(len(ALONE_CASES)))
+def test_direct_tensors_in_launches_of_their_own(case):
+    """A direct tensor above 64 MiB a rank, or the last one, needs no table cut and uploaded (a
+    call made once pays for it): same bits as in a table."""
+    numel, n, threshold, half, compress, off, want_alone = ALONE_CASES[case]
+    say(f"direct tensors alone, case {case}")
+    rng = np.random.default_rng(5400 + case)
+    dtype = np.float16 if half else np.float32
+    host = [[(rng.standard_normal(k) * 0.01).astype(dtype) for k in numel] for _ in range(n)]
+    dev = [[to_gpu_rows(x[None], off)[0][0] for x in row] for row in host]
+    ar = hv.FusedAllreduce(dev, compress=compress, threshold_bytes=threshold)
+    ar()
+    torch.cuda.synchronize()
+    alone = [t for c in ar._cycles if c.table is None for i in c.members for t in ar.buckets[i].tensors]
+    assert alone == want_alone
+    assert len(ar.kernel_sequence()) == len(ar._cycles) <= 2
+    want = native.allreduce(host, "average", compress=compress, threshold=threshold)
+    for r in range(n):
+        for t in range(len(numel)):
+            assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
