@@ -47,18 +47,23 @@ def test_tensors(n, kind, offsets):
     root = n // 2
     say(f"tensor broadcast n={n} {kind} {offsets}")
     x = [[rng.integers(0, 256, size=s, dtype=np.uint8) for s in sizes] for _ in range(n)]
-    for dense in (False, True):  # the object's own layout, and the densest one through the C entry
+    for layout in ("object", "dense", "pages"):  # the one it chose, and either through the C entries
         bases, views = tensor_views(x, sizes, off)
         tb = hv.TensorBroadcast(views)
-        if dense:
+        if layout == "dense":
             hv.hvdx_broadcast_tensors(*tb._args, root, tb._stream(None))
+        elif layout == "pages":
+            starts, extent = hv._call_layout(sizes, [v.data_ptr() for v in views[0]], None, 1 << 60)
+            table = torch.tensor(starts, dtype=torch.int64, device="cuda")
+            hv.hvdx_broadcast_tensors_placed(*tb._args[:2], table.data_ptr(), len(sizes), extent, tb.total, n, root,
+                                             tb._stream(None))
         else:
             tb(root)
         torch.cuda.synchronize()
         got = host_state(views)
         for r in range(n):
             for t in range(len(sizes)):
-                assert_bits_equal(got[r][t], x[root][t], f"dense={dense} rank {r} tensor {t}")
+                assert_bits_equal(got[r][t], x[root][t], f"{layout} rank {r} tensor {t}")
         everything = torch.cat([b for row in bases for b in row]).cpu().numpy()
         at = 0
         for _ in range(n):

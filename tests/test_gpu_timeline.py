@@ -127,8 +127,9 @@ def test_broadcasts_record_the_tensors_bytes():
     """A list's broadcast in one launch records step -1 and the same bytes as the chain's steps,
     not its virtual space, which keeps each tensor in pages of its own."""
     say("timeline of broadcasts")
-    per_rank = tensors(4, [7, 4000, 0, 100, 1, 3])
+    per_rank = tensors(4, [7, 40000, 0, 100, 10001, 3])
     tb = hv.TensorBroadcast(per_rank)
+    assert tb._call_args[4] > tb.total + 4096  # a space with pages
     flat = tensors(3, [1001])
     with hv.Timeline(capacity=100) as tl:
         tb(1)

@@ -231,12 +231,10 @@ def dense_starts(sizes):
 
 
 def paged_starts(sizes, addresses):
-    """TensorBroadcast's space: every tensor in pages of its own, where rank 0's address lies in one."""
-    starts, end = [], 0
-    for b, p in zip(sizes, addresses):
-        starts.append(-(-end // 4096) * 4096 + p % 4096)
-        end = starts[-1] + b
-    return starts, end
+    """The space with every tensor in pages of its own, where rank 0's address lies in one."""
+    import paper_1802_05799_amd as hv
+
+    return hv._call_layout(sizes, addresses, None, 1 << 60)
 
 
 def check_whole_list(sizes, starts, extent, U, **kw):
@@ -266,6 +264,21 @@ def test_whole_tensor_broadcast_stores_every_byte(U):
         for anywhere in (False, True):  # an empty tensor's address is 0
             at = [int(rng.integers(0, 1 << 20)) if b and anywhere else 256 * i if b else 0 for i, b in enumerate(sizes)]
             check_whole_list(sizes, *paged_starts(sizes, at), U)
+
+
+def test_space_of_a_list_broadcast():
+    """Pages of their own for tensors that fill them; the dense layout for many short ones, whose
+    pages would be more than twice their bytes."""
+    import paper_1802_05799_amd as hv
+
+    for sizes, pages in (([9000] * 50, True), ([5000, 1, 70_000], True), ([100], True), ([64] * 3000, False),
+                         ([2000] * 100, False), ([], True), ([0, 0], True)):
+        dense, total = hv.hvdx_broadcast_layout(sizes)
+        at = [256 * i if b else 0 for i, b in enumerate(sizes)]
+        got = hv._call_layout(sizes, at, dense, total)
+        assert got == (paged_starts(sizes, at) if pages and sizes and total else (dense, total))
+        if any(sizes):
+            check_whole_list(sizes, *got, 2)
 
 
 def test_whole_tensor_broadcast_leaves_empty_tensors_alone():
