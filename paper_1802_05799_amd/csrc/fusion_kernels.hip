@@ -718,12 +718,14 @@ __global__ __launch_bounds__(Cfg::BS) HVDX_COPY_ATTR void unpack_pair_kernel(Cop
 // thread takes one 16-byte buffer vector of every rank's tensors through all 2(N-1) ring steps
 // in registers and stores the result to every rank's.  The bound is latency: with each step's
 // message through the buffers a thread waited for 2(N-1) memory round trips one after the other
-// (15.9 us for the toy list on 4 ranks); now the loads go out eight ranks at a time.  Vectors of
-// padding only are skipped; edge vectors and those that cross a chunk end go element by
-// element.  A block serves one tile of 256 vectors for all ranks.
+// (15.9 us for the toy list on 4 ranks); now the loads go out R ranks at a time: eight, and two
+// where that is all there are (3 ranks, 1,000 tensors of 1,000 binary16 elements: 20.1 us with
+// eight, which load the last rank seven times).  Vectors of padding only are skipped; edge
+// vectors and those that cross a chunk end go element by element.  A block serves one tile of
+// 256 vectors for all ranks.
 using SmallCfg = CopyCfg<1, 1, 0, false, false>;
 
-template <typename TT, typename TB, int DIV>
+template <typename TT, typename TB, int DIV, int R>
 __global__ __launch_bounds__(kBlock) void small_cycle_kernel(const void* const* __restrict__ tensors,
                                                              const int64_t* __restrict__ numel,
                                                              const int64_t* __restrict__ offset, int ntensors,
@@ -746,7 +748,6 @@ __global__ __launch_bounds__(kBlock) void small_cycle_kernel(const void* const* 
   // The ring of what `load` finds at (rank, tensor t), from rank c on, in its order.
   auto ring = [&](int c, auto load, auto store) {
     auto rank = [&](int k) { return c + k < n ? c + k : c + k - n; };
-    constexpr int R = 8;
     auto sum = load(rank(0));
     for (int k0 = 1; k0 < n; k0 += R) {
       decltype(sum) x[R];
@@ -1474,8 +1475,10 @@ hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, 
                               hipStream_t stream) {
   const dim3 grid(tiles_for<SmallCfg>(count, vec_elems(tensor_dtype, buf_dtype))), block(kBlock);
 #define HVDX_SMALL(TT, TB, DIV) \
-  HVDX_LAUNCH((small_cycle_kernel<TT, TB, DIV>), grid, block, 0, stream, tensors, numel, offset, ntensors, a, \
-              count)
+  if (a.n <= 3) HVDX_LAUNCH((small_cycle_kernel<TT, TB, DIV, 2>), grid, block, 0, stream, tensors, numel, offset, \
+                            ntensors, a, count); \
+  else HVDX_LAUNCH((small_cycle_kernel<TT, TB, DIV, 8>), grid, block, 0, stream, tensors, numel, offset, ntensors, a, \
+                   count)
 #define HVDX_SMALL_D(TT, TB) \
   if (divmode == DIV_NONE) { HVDX_SMALL(TT, TB, DIV_NONE); } \
   else if (divmode == DIV_POW2) { HVDX_SMALL(TT, TB, DIV_POW2); } \

@@ -54,7 +54,7 @@ def test_ring_small_unaligned_and_special_values():
 
 
 SMALL_CASES = [
-    # (numel list, nranks, buffer dtype, align bytes, op)
+    # (numel list, nranks, buffer dtype, align bytes, op[, tensor dtype: binary32])
     ([7, 64, 100, 1000, 4608, 4096, 513, 10000], 4, np.float32, 16, "average"),  # the tiny workload
     ([7, 64, 100, 1000, 4608, 4096, 513, 10000], 1, np.float32, 16, "average"),  # one rank
     ([7, 64, 100, 1000, 4608, 4096, 513, 10000], 2, np.float16, 16, "sum"),  # binary16 buffer
@@ -66,28 +66,36 @@ SMALL_CASES = [
     ([3000, 1, 2, 50000, 64, 64, 64, 128 * 1024, 9], 13, np.float16, 2, "average"),
     ([5000, 300, 70000], 32, np.float32, 16, "average"),
     ([5000, 300, 70001], 128, np.float16, 2, "average"),  # the most ranks a call takes
+    # binary16 tensors: up to 3 ranks and more, each way of dividing, every edge
+    ([7, 64, 100, 1000, 4608, 4096, 513, 10000], 1, np.float16, 16, "average", np.float16),
+    ([7, 64, 100, 1000, 4608, 4096, 513, 10000], 2, np.float16, 16, "average", np.float16),
+    ([0, 1, 0, 3, 5, 0, 0, 2, 17, 3001], 3, np.float16, 16, "sum", np.float16),
+    ([33, 31, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10000], 3, np.float16, 2, "average", np.float16),
+    ([257] * 40 + [7000, 3, 900], 4, np.float16, 2, "average", np.float16),
+    ([33, 31, 1, 2, 3, 4, 5, 6, 7, 8, 9, 100000], 7, np.float16, 2, "average", np.float16),
+    ([3000, 1, 2, 50000, 64, 64, 64, 9], 16, np.float16, 16, "sum", np.float16),
 ]
 
 
 @pytest.mark.parametrize("misalign", [False, True], ids=["aligned", "misaligned"])
 @pytest.mark.parametrize("case", range(len(SMALL_CASES)))
 def test_fuse_allreduce_small_matches_oracle(case, misalign):
-    numel, n, buf_np, align, op = SMALL_CASES[case]
+    numel, n, buf_np, align, op, tensor_np = (*SMALL_CASES[case], np.float32)[:6]
     rng = np.random.default_rng(210 + case)
-    host, dev, keep = make_tensors(rng, n, numel, np.float32, misalign)
+    host, dev, keep = make_tensors(rng, n, numel, tensor_np, misalign)
     (b,) = fusion.fuse_plan(numel, np.dtype(buf_np).itemsize, 1 << 40, align)
     say(f"small cycle case={case} n={n} buffer={np.dtype(buf_np).name} misalign={misalign} count={b.count}")
     ptrs, nm, off = descriptors(dev, b, numel)
     bufs = [torch.full((max(b.count, 1),), 7.0, dtype=torch.float32 if buf_np == np.float32 else torch.float16,
                        device="cuda") for _ in range(n)]
-    hv.hvdx_fuse_allreduce_small(ptrs.data_ptr(), nm.data_ptr(), off.data_ptr(), len(numel), hv.FLOAT32,
+    hv.hvdx_fuse_allreduce_small(ptrs.data_ptr(), nm.data_ptr(), off.data_ptr(), len(numel), NP_TO_HV[np.dtype(tensor_np)],
                                  [x.data_ptr() for x in bufs], b.count, NP_TO_HV[np.dtype(buf_np)], n, OPS[op],
                                  torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     work = np.stack([fusion.pack(host[r], b, buf_np) for r in range(n)])
     ring.ring_allreduce(work, op)
     for r in range(n):
-        want = fusion.unpack(work[r], b, numel, np.float32)
+        want = fusion.unpack(work[r], b, numel, tensor_np)
         for t in range(len(numel)):
             assert_bits_equal(dev[r][t].cpu().numpy(), want[t], f"rank {r} tensor {t}")
 
