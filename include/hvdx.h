@@ -441,7 +441,8 @@ int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int 
  * Limit: hvdx_ring_workspace_bytes(nranks, count, dtype, compress) must not exceed
  * hvdx_ring_noalloc_max_bytes() (64 MiB: e.g. 8 ranks of up to 4,194,304 binary32
  * elements compressed); larger requests return HVDX_ERR_WORKSPACE before any HIP
- * call.  Without compression any size works.
+ * call, as they did when the ring needed such a workspace (hvdx_ring_allreduce_whole
+ * takes them).  Without compression any size works.
  * Errors: as hvdx_ring_allreduce; HVDX_ERR_WORKSPACE beyond the limit.
  */
 int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,

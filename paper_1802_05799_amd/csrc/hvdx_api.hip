@@ -1151,7 +1151,7 @@ size_t hvdx_ring_noalloc_max_bytes(void) { return (size_t)64 << 20; }
 int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                                 void* stream) {
   static const char* what = "hvdx_ring_allreduce_noalloc";
-  // every argument check first (no HIP call before them), the workspace's size included
+  // every argument check first (no HIP call before them), the call's limit included
   int rc = check_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, nullptr, 0, what);
   if (rc) return rc;
   if (compress != HVDX_COMPRESS_NONE && compress != HVDX_COMPRESS_FP16)
@@ -1160,8 +1160,8 @@ int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, in
     return fail(HVDX_ERR_INVALID, "%s: fp16 compression needs float32 buffers", what);
   const size_t need = hvdx_ring_workspace_bytes(nranks, count, dtype, compress), most = hvdx_ring_noalloc_max_bytes();
   if (need > most)
-    return fail(HVDX_ERR_WORKSPACE, "%s: %d ranks of %lld elements need %zu bytes of wire workspace; the static limit "
-                "is %zu (use hvdx_ring_allreduce with a workspace)", what, nranks, (long long)count, need, most);
+    return fail(HVDX_ERR_WORKSPACE, "%s: %d ranks of %lld elements are %zu bytes in binary16, over this call's static "
+                "limit of %zu (hvdx_ring_allreduce_whole has none)", what, nranks, (long long)count, need, most);
   if (count == 0) return HVDX_OK;
   if (nranks == 1)
     return hvdx_ring_allreduce(bufs, nranks, count, dtype, op, compress, nullptr, 0, stream);

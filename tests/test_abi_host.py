@@ -321,6 +321,16 @@ def test_fused_allreduce_rejects_overlapping_tensors():
         cycle._check_disjoint([[base[0:101], b], [c, base[500:600]]])  # one element shared
 
 
+def test_noalloc_limit_names_the_call_without_one():
+    """Beyond its limit the call is refused, with the call that takes such a request (which needs
+    no workspace either)."""
+    n, count = 8, 4_194_304 + 1
+    assert status_of(hv.hvdx_ring_allreduce_noalloc, bufs(n, count), n, count, hv.FLOAT32, hv.SUM,
+                     hv.COMPRESS_FP16) == hv.ERR_WORKSPACE
+    text = hv.hvdx_last_error()
+    assert "hvdx_ring_allreduce_whole" in text and "workspace" not in text and str(64 << 20) in text
+
+
 def test_noalloc_ring_argument_checks():
     """The allocation-free ring checks its arguments and the static workspace's size
     before any HIP call (so these run without a GPU)."""
