@@ -112,10 +112,12 @@ __device__ __forceinline__ T* uniform_here(T* p) {
 }
 
 // One vector per lane.  ptr(k) is the address of the stretch's first element on the k-th
-// rank of its ring (rank c+k mod N), readable, if meaningless, up to the next multiple of 16
-// past the last one; MT is FoldTypes::vec or, unaligned, ::uvec.
+// rank of its ring (rank c+k mod N).  The last burst reads, but does not use, up to ptr(n+B-2):
+// with the ring's ranks from rank c on, entry c+n+B-2 <= 2n+B-3 of a list of 2n; MT is
+// FoldTypes::vec or, unaligned, ::uvec.
 template <typename TT, typename TB, int B, typename MT, typename Ptr>
 __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, int mode) {
+  static_assert(B - 2 <= kFoldPad, "a list of 2n rank pointers is followed by kFoldPad more");
   using F = FoldTypes<TT, TB>;
   using vec = typename F::vec;
   const unsigned off = threadIdx.x * 16u;  // unsigned: a scalar base and a 32-bit offset per access

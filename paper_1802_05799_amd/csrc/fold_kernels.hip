@@ -105,7 +105,7 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
   const dim3 grid((unsigned)bx, (unsigned)a.n);
   const int burst = fold_burst(a.n);
   const unsigned lds = fold_holds(bx * a.n, a.q * a.n + a.rem, a.n, tensor_dtype) ? fold_lds(a.n, burst) : 0;
-  RingPtrs ptrs;
+  RingPtrs ptrs{};  // the pad is read, if not used
   for (int r = 0; r < a.n; ++r) ptrs.p[r] = ptrs.p[a.n + r] = bufs.p[r];
   with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
     HVDX_LAUNCH((fold_flat_kernel<decltype(tt), decltype(tb), b.value>), grid, dim3(kFoldLanes), lds, stream, ptrs, a,

@@ -17,10 +17,8 @@
 
 #include "ring_math.hpp"
 
-
 namespace hvdx {
 namespace {
-
 
 // Shape of a copy kernel: POS buffer vectors per lane in a row (a row is BS*POS
 // vectors for BS threads per block), SUB rows per block (one tensor lookup serves them all), RB ranks whose

@@ -40,7 +40,6 @@ struct Vec<_Float16> {
   static constexpr int n = 8;
 };
 
-
 template <int DIV>
 __device__ __forceinline__ float finish(float v, const RingArgs& a) {
   if constexpr (DIV == DIV_POW2) return v * a.inv;
