@@ -36,8 +36,8 @@ TILED_REPLACE_IN_TENSORS, TILED_ADD_FROM_TENSORS = 1, 2  # the HVDX_TILED_* bits
 # FusedAllreduce arguments of each way of running the fusion buffers
 BUFFER_MODES = {"ring_on_tensors": {}, "copy_in": {"add_from_tensors": False},
                 "paper_copies": {"replace_in_tensors": False}}
-# ... and what makes the default run the ring's steps in launches of their own (buckets of a few MiB excepted)
-PER_STEP = {"small_bucket_bytes": (4 << 20) - 1}
+# ... and what makes the default run every bucket's ring steps in launches of their own
+PER_STEP = {"small_bucket_bytes": 0}
 
 
 def parse():
@@ -119,8 +119,8 @@ KIND_CODE = {"pack": 0, "rs": 1, "ag": 2, "unpack": 3, "ring": 4, "rs_ag": 6, "f
 
 def kernel_name(ar, kind, bi):
     b = ar.buckets[bi[0] if isinstance(bi, tuple) else bi]
-    if kind in ("cycle_small", "ring_small"):  # of the fusion buffers, of the direct tensors: one kernel
-        return "whole_ring"
+    if kind == "ring_small" or kind == "cycle_small" and getattr(ar, "_cycles", None) is not None:
+        return "whole_ring"  # the per-step path's small fusion buffers have a kernel of their own
     if kind in ("rs", "ag", "rs_ag"):
         flags = 0 if b.direct else ar.tiled_flags
         # a compressed bucket's steps that read or write binary32 tensors are the compressed ring's
@@ -269,6 +269,17 @@ def hbm_fracs(r):
     path_bytes = sum(v["bytes"] for v in r["kernels"].values()) / r["steps"]
     return (round(ring_bytes / (ring_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if ring_ms else None,
             round(path_bytes / (r["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4))
+
+
+def fracs(kernels):
+    return {k: v["hbm_frac"] and round(v["hbm_frac"], 4) for k, v in kernels.items()}
+
+
+def flushed(whole, steps, ring_frac, path_frac):
+    """A workload's figures with the Infinity Cache flushed: the one launch, and the ring in steps."""
+    return {"ms_per_step": round(whole["ms_per_step"], 4), "algbw_GBps": round(whole["algbw_GBps"], 2),
+            "ring_hbm_frac": ring_frac, "path_hbm_frac": path_frac, "kernels_hbm_frac": fracs(whole["kernels"]),
+            "step_kernels_hbm_frac": fracs(steps["kernels"])}
 
 
 def measure_broadcast(name, steps, warmup=2):
@@ -692,11 +703,7 @@ def main():
                 "per_step_ms": round(per_step["ms_per_step"], 4),
                 "ring_hbm_frac": ring_frac,
                 "path_hbm_frac": path_frac,
-                "mall_flushed": {"ms_per_step": round(f["ms_per_step"], 4),
-                                 "algbw_GBps": round(f["algbw_GBps"], 2),
-                                 "ring_hbm_frac": f_ring, "path_hbm_frac": f_path,
-                                 "kernels_hbm_frac": {k: v["hbm_frac"] and round(v["hbm_frac"], 4)
-                                                      for x in (f, fs) for k, v in x["kernels"].items()}},
+                "mall_flushed": flushed(f, fs, f_ring, f_path),
                 "algbw_GBps": round(r["algbw_GBps"], 2),
                 "busbw_GBps": round(r["busbw_GBps"], 2),
                 "kernels": {k: {"avg_us": round(v["avg_us"], 2), "GBps": v["GBps"] and round(v["GBps"], 1),
@@ -707,9 +714,10 @@ def main():
                                      "share": round(v["share"], 4)} for k, v in per_step["kernels"].items()},
             }
 
-    # one launch (the default), then the steps in launches of their own: the fusion buffers' ring on
-    # the tensors, and the paper's copies: the copy-in kept (fused with adding step 0), and the whole ring in the buffers between
-    # the copy-in and the copy-out (fused with the first and last steps); same bits
+    # one launch (the default), then the steps in launches of their own: the fusion buffers' ring
+    # on the tensors, and the paper's copies: the copy-in kept (fused with adding step 0), and the
+    # whole ring in the buffers between the copy-in and the copy-out (fused with the first and last
+    # steps); same bits
     buffer_modes = {}
     if not args.no_per_config:
         for name in ("resnet50", "inceptionv3", "vgg16", "vgg16fp16"):

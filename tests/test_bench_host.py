@@ -100,6 +100,28 @@ def test_a_launch_serving_two_buckets_counts_both():
     assert bench.kernel_bytes(ar, "rs", (0, 1), 1) == 3 * 4 * (300 + 280)
 
 
+def test_one_launch_kernels_report_what_runs():
+    """A fusion buffer's one launch is the table's kernel where the whole call is (an object with
+    _cycles), hvdx_fuse_allreduce_small's on the per-step path; a direct tensor's is the flat one."""
+    ar = fake_allreduce(4, [5, 100], [([0], 8, False), ([1], 100, True)])
+    assert bench.kernel_name(ar, "cycle_small", 0) == "cycle_small"
+    assert bench.kernel_name(ar, "ring_small", 1) == "whole_ring"
+    ar._cycles = []
+    assert bench.kernel_name(ar, "cycle_small", (0, 0)) == "whole_ring"
+    assert bench.kernel_name(ar, "ring_small", 1) == "whole_ring"
+    assert bench.PER_STEP == {"small_bucket_bytes": 0}  # no bucket takes one launch instead of its steps
+
+
+def test_fractions_of_the_steps_do_not_replace_the_one_launch():
+    kernels = {"whole_ring": {"hbm_frac": 0.75001}, "x": {"hbm_frac": None}}
+    steps = {"rs_step_f32": {"hbm_frac": 0.8}, "whole_ring": {"hbm_frac": 0.1}}
+    assert bench.fracs(kernels) == {"whole_ring": 0.75, "x": None}
+    got = bench.flushed({"ms_per_step": 1.0, "algbw_GBps": 2.0, "kernels": kernels}, {"kernels": steps}, 0.8, 0.7)
+    assert got["kernels_hbm_frac"] == {"whole_ring": 0.75, "x": None}
+    assert got["step_kernels_hbm_frac"] == {"rs_step_f32": 0.8, "whole_ring": 0.1}
+    assert got["ring_hbm_frac"] == 0.8 and got["path_hbm_frac"] == 0.7 and got["ms_per_step"] == 1.0
+
+
 REAL_NAMES = {
     "void hvdx::(anonymous namespace)::unpack_kernel<float, float, hvdx::(anonymous namespace)::CopyCfg<2, 2, 2, "
     "true, true, false, 1>, true>(hvdx::RankPtrs, long, void* const*, long const*, long const*, int, int, int, "
