@@ -300,17 +300,17 @@ def measure_broadcast(name, steps, warmup=2):
     flat_ptrs = [x.data_ptr() for x in storage]
     flat_bytes = storage[0].numel() * 4
 
-    def timed(fn):
+    def timed(fn):  # the median call: what the host stalls (tens of ms at times) is an outlier
         for _ in range(warmup):
             fn()
         torch.cuda.synchronize()
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record(stream)
-        for _ in range(steps):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(steps + 1)]
+        ev[0].record(stream)
+        for e in ev[1:]:
             fn()
-        b.record(stream)
+            e.record(stream)
         torch.cuda.synchronize()
-        return a.elapsed_time(b) / steps
+        return sorted(a.elapsed_time(b) for a, b in zip(ev, ev[1:]))[steps // 2]
 
     def per_tensor_chains():
         for ts in zip(*per_rank):
