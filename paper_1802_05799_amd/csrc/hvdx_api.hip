@@ -1012,8 +1012,6 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
   }
   const int64_t npointers = hvdx::fold_pointers(ntensors, nranks);
   const int64_t ptr_bytes = npointers * (int64_t)sizeof(void*);  // a multiple of 16
-  void** ptrs = static_cast<void**>(table);
-  hvdx::FoldTile* tiles = reinterpret_cast<hvdx::FoldTile*>(static_cast<char*>(table) + ptr_bytes);
   const int64_t room = table && capacity >= ptr_bytes ? (capacity - ptr_bytes) / (int64_t)sizeof(hvdx::FoldTile) : -1;
   const int64_t vec = hvdx::tile_vec_elems(tensor_dtype, buf_dtype);
   int64_t n = 0, elements = 0, pieces = 0;
@@ -1021,6 +1019,7 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
     const int64_t q = bucket_count[bucket_of[t]] / nranks;
     pieces += q ? std::min<int64_t>(nranks, numel[t] / q + 2) : std::min<int64_t>(nranks, numel[t]);
     elements += numel[t];
+    if (elements > (INT64_MAX >> 4)) return fail(HVDX_ERR_INVALID, "%s: too many elements", what);
   }
   *stretches = hvdx::fold_stretches(elements / (64 * vec), pieces);
   const bool narrow = *stretches == 1;
@@ -1029,6 +1028,8 @@ int64_t hvdx_fuse_cycle_table(void* const* tensors, const int64_t* numel, const 
     *ntiles = n = elements / tile + 3 * pieces;
     return ptr_bytes + n * (int64_t)sizeof(hvdx::FoldTile);
   }
+  void** ptrs = static_cast<void**>(table);
+  hvdx::FoldTile* tiles = room >= 0 ? reinterpret_cast<hvdx::FoldTile*>(ptrs + npointers) : nullptr;
   for (int i = 0; i < hvdx::kFoldPad && room >= 0; ++i) ptrs[npointers - hvdx::kFoldPad + i] = nullptr;
   for (int t = 0; t < ntensors; ++t) {
     for (int r = 0; r < nranks && room >= 0; ++r)

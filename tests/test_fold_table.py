@@ -86,6 +86,11 @@ def test_table_argument_errors():
         with pytest.raises(hv.HvdxError) as e:
             hv.hvdx_fuse_cycle_table(**{**ok, **bad})
         assert e.value.status == status, bad
+    huge = dict(tensors=[1 << 32] * 34, numel=[1 << 59] * 17, offset=[0] * 17, bucket_of=list(range(17)),
+                bucket_count=[1 << 59] * 17)
+    with pytest.raises(hv.HvdxError) as e:  # more elements than their sum holds
+        hv.hvdx_fuse_cycle_table(**{**ok, **huge})
+    assert e.value.status == hv.ERR_INVALID
     for args in ((0, 1, 4, 4, 9, hv.FLOAT32, hv.FLOAT32, 2, hv.SUM, False),
                  (256, 1, 4, 4, 9, hv.FLOAT32, hv.FLOAT32, 129, hv.SUM, False),
                  (256, 1, 4, 4, 9, hv.FLOAT32, 7, 2, hv.SUM, False), (256, 1, 4, 4, 9, hv.FLOAT32, hv.FLOAT32, 2, 5, False),

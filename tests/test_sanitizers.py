@@ -4,9 +4,9 @@
    tests/test_oracle_native.py (all but the planted-mistake builds, which compile their
    own copies): plan, ring, copies, binary16 conversions, OpenMP threads.
 2. libhvdx's host code (every .hip source built with hipcc, the sanitizers applied to
-   the host side only) runs tests/test_abi_host.py: the fusion plan, the ring
-   partition, the broadcast layout and every argument check, through the C-ABI, with no
-   GPU.
+   the host side only) runs tests/test_abi_host.py and tests/test_fold_table.py: the fusion
+   plan, the ring partition, the broadcast layout, every argument check and the one-launch
+   cycle's table, through the C-ABI, with no GPU.
 Each run is a child process with the sanitizer runtime preloaded; any report ends it
 with an error.  A planted out-of-bounds write and a planted signed overflow, built the
 same two ways, must be caught, so a silent harness cannot pass.
@@ -111,7 +111,7 @@ def test_oracle_under_sanitizers(tmp_path, gcc_asan):
     script = drive(str(pkg), os.path.join(ROOT, "tests", "test_oracle_native.py"), ["-k", "not planted"])
     script = script.replace("import pytest", check + "\nimport pytest", 1)
     r = child(script, gcc_asan)
-    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-3000:])
+    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[:3000])
     assert " passed" in r.stdout
 
 
@@ -137,8 +137,9 @@ def test_library_host_code_under_sanitizers(tmp_path, clang_asan):
     assert planted_caught(str(tmp_path / "libplanted.so"), clang_asan) is None
 
     check = f"import paper_1802_05799_amd as hv; assert hv.LIB_PATH == {str(pkg / 'libhvdx.so')!r}, hv.LIB_PATH"
-    script = drive(str(pkg.parent), os.path.join(ROOT, "tests", "test_abi_host.py"))
+    script = drive(str(pkg.parent), os.path.join(ROOT, "tests", "test_abi_host.py"),
+                   [os.path.join(ROOT, "tests", "test_fold_table.py")])
     script = script.replace("import pytest", check + "\nimport pytest", 1)
     r = child(script, clang_asan)
-    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-3000:])
+    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[:3000])
     assert " passed" in r.stdout
