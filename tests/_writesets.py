@@ -31,6 +31,8 @@ class Knobs:
     fused_own_from_buffer: bool = False  # the fused step reads the owner's value from its buffer (False)
     xcd_shift: int = 0  # added to a block's XCD in tile_block() (0)
     bucket_end_shift: int = 0  # added to each bucket's first launch tile in ring_bucket() (0)
+    edge_lanes_short: int = 0  # lanes with a single element that store nothing (0)
+    part_shift: int = 0  # added to the distance of a wide tile's stretches (0)
     empty_is_read: bool = False  # the one-launch broadcast reads an empty tensor's first byte (False)
     clamp_tail: bool = True  # a one-launch broadcast's short last unit is the last 16 bytes (True)
 
@@ -412,9 +414,9 @@ def copy_pair_launch(kind, n, buckets, tensor_es, buf_es, k=K):
 
 
 def small_cycle_threads(n, count, numel, offset, V, k=K):
-    """small_cycle_kernel: per buffer position, the thread that takes it through the
-    copy-in, every ring step and the copy-out (-1 for padding that no thread touches),
-    and per rank and tensor how often each tensor element is written back."""
+    """small_cycle_kernel: per buffer position, the thread that takes it from every rank's
+    tensor through every ring step (-1 for padding that no thread touches), and per rank
+    and tensor how often each tensor element is stored."""
     cfg = SMALL_CFG
     tile = cfg.tile_vecs * V
     lay = Layout(numel, offset)
@@ -447,13 +449,58 @@ def small_cycle_threads(n, count, numel, offset, V, k=K):
     return owner, clash, tw
 
 
-def chain_threads(count, V, n, fold=False, k=K):
-    """fold_flat_kernel (`fold` or not, one kernel): how many lanes take each element.  Block
-    row c is chunk c, whose stretches are its pieces of the grid of 64*V elements; a lane
-    takes one whole vector of its stretch, then the first lanes one element each of the rest."""
+def fold_burst(n):
+    """fold_burst(): the ranks' loads that a wavefront of the one-launch ring issues at once."""
+    if n < 8:
+        return max(n, 2)
+    if n <= 24:
+        return (n + 1) // 2
+    for b in range(16, 9, -1):
+        if n % b == 0:
+            return b
+    bursts = (n + 11) // 12
+    return (n + bursts - 1) // bursts
+
+
+BURST_RANKS = [2, 3, 4, 5, 6, 7, 16, 17, 20, 22, 24, 26, 28, 30, 32]  # a rank count for each burst
+FOLD_PAD = 16  # pointers after a list of rank pointers (kFoldPad)
+
+
+def fold_stretch(m, V, aligned, head, k=K):
+    """fold_stretch(): (stored, loaded) element indices of a wavefront's stretch of m elements, with
+    repetition.  With whole vectors and single elements both (fold_edges) every lane loads one of
+    each, lanes past the last ones that one again."""
+    head = min(head, m)
+    vecs = (m - head) // V
+    rest = m - vecs * V
+    assert rest <= 64 and vecs <= 64, "more than a lane each"
+    stored, loaded = [], []
+    for lane in range(64):
+        e = head + (lane + k.lane_shift) * V
+        if vecs and rest:
+            i = min(lane, rest - 1)
+            one = i if i < head else vecs * V + i
+            loaded += list(range(head + min(lane, vecs - 1) * V, head + min(lane, vecs - 1) * V + V)) + [one]
+            stored += list(range(e, e + V)) if lane < vecs else []
+            stored += [one] if lane < rest - k.edge_lanes_short else []
+        elif lane < vecs:
+            assert head == 0
+            loaded += range(e, e + V)
+            stored += range(e, e + V)
+        elif lane < rest:
+            loaded.append(lane)
+            stored.append(lane)
+        if aligned and vecs:
+            assert (e - head) % V == 0
+    return np.asarray(stored, np.int64), np.asarray(loaded, np.int64)
+
+
+def fold_flat(count, V, n, aligned=True, k=K):
+    """fold_flat_kernel: how often each element is stored (to every rank), and loaded.  Block row c is
+    chunk c, whose stretches are its pieces of the grid of 64*V elements."""
     S = 64 * V
     q, rem = divmod(count, n)
-    hits = np.zeros(count, np.int64)
+    hits, loads = np.zeros(count, np.int64), np.zeros(count, np.int64)
     gx = min((q + (1 if rem else 0)) // S + 2, 1 << 22)
     for c in range(n):
         start, length = chunk(c, q, rem)
@@ -462,15 +509,29 @@ def chain_threads(count, V, n, fold=False, k=K):
             g = start // S + bx
             while g * S < end:
                 e0, e1 = max(g * S, start), min((g + 1) * S, end)
-                vecs, rest = divmod(e1 - e0, V)
-                for lane in range(64):
-                    if lane < vecs:
-                        e = e0 + (lane + k.lane_shift) * V
-                        add(hits, np.arange(e, e + V))
-                    if lane < rest:
-                        add(hits, np.array([e0 + vecs * V + lane]))
+                w, r = fold_stretch(e1 - e0, V, aligned and e0 % V == 0, 0, k)
+                add(hits, e0 + w)
+                add(loads, e0 + r, "read")
                 g += gx
-    return hits
+    return hits, loads
+
+
+def fold_table(numel, tiles, stretches, V, k=K):
+    """fold_table_kernel over a table's tiles (first element, tensor, elements, first rank, aligned,
+    head): per tensor, how often each element is stored to every rank, and loaded."""
+    S = 64 * V
+    w = [np.zeros(m, np.int64) for m in numel]
+    r = [np.zeros(m, np.int64) for m in numel]
+    for b in range(len(tiles) * stretches):
+        li, t, length, _, aligned, head = tiles[b // stretches]
+        part = b % stretches * (S + k.part_shift)
+        left = length - part
+        if left <= 0:
+            continue
+        stored, loaded = fold_stretch(min(left, S), V, aligned, head, k)
+        add(w[t], li + part + stored)
+        add(r[t], li + part + loaded, "read")
+    return w, r
 
 
 def bcast_step(n, nbytes, root, step, k=K):
@@ -571,6 +632,27 @@ def unit_bytes(at, length, k=K):
         return None
     e = 0 if at < 0 else length - 16 if at + 16 > length and k.clamp_tail else at
     return np.arange(e, e + 16)
+
+
+def bcast_whole(nbytes, address, U, k=K):
+    """bcast_kernel: how often each byte is stored to a receiving rank; `address` is the first
+    receiver's, whose multiples of a stretch's bytes cut the buffer."""
+    w = np.zeros(nbytes, np.int64)
+    tile = 64 * U * 16
+    shift = 0 if nbytes < 16 else address % tile
+    blocks = -(-(nbytes + shift) // tile)
+    for b in range(blocks):
+        p0 = b * tile - shift
+        for lane in range(64):
+            if nbytes < 16:
+                if p0 <= 0 and lane < nbytes:
+                    add(w, [lane])
+                continue
+            for u in range(U):
+                e = unit_bytes(p0 + (u * 64 + lane + k.lane_shift) * 16, nbytes, k)
+                if e is not None:
+                    add(w, e)
+    return w
 
 
 def bcast_tensors_whole(nbytes, start, extent, U, k=K):

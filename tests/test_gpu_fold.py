@@ -1,5 +1,5 @@
-"""The one-launch kernels at the edges of their shapes: bursts of 8, 16 and 32 ranks and
-their remainders, stretches of 64 vectors that a chunk ends inside, buffers aligned to
+"""The one-launch kernels at the edges of their shapes: every burst (2 to 16 ranks' loads at once)
+and its remainders, stretches of 64 vectors that a chunk ends inside, buffers aligned to
 their elements only.  Bit for bit against the oracle's ring (no tolerance: the order of
 additions and every rounding are the ring's)."""
 import numpy as np
@@ -8,6 +8,7 @@ import torch
 
 import paper_1802_05799_amd as hv
 from _gpu import NP_TO_HV, OPS, assert_bits_equal, from_gpu_rows, say, to_gpu_rows
+from _writesets import BURST_RANKS, fold_burst
 from oracle import allreduce, native
 from test_gpu_ring import inputs, oracle_ring
 
@@ -48,6 +49,32 @@ def test_flat_buffers_compressed(n):
             hv.hvdx_fold_allreduce([r.data_ptr() for r in rows], n, count, hv.FLOAT32, hv.AVERAGE, hv.COMPRESS_FP16,
                                    torch.cuda.current_stream().cuda_stream)
             assert_bits_equal(from_gpu_rows(rows), want, f"n={n} count={count}")
+
+
+@pytest.mark.parametrize("n", BURST_RANKS)
+def test_every_burst(n):
+    """Each instantiation of either kernel: flat buffers and a list whose tensors lie differently
+    to 16 bytes on each rank, binary32, binary16, and binary32 rounded to binary16."""
+    rng = np.random.default_rng(5150 + n)
+    numel = [n * 300 + 7, 513, 3]
+    for half, compress in ((False, False), (True, False), (False, True)):
+        dtype = np.float16 if half else np.float32
+        say(f"burst of {fold_burst(n)}: n={n} half={half} compress={compress}")
+        x = inputs(rng, n, n * 300 + 5, dtype)
+        for offset in (0, 1):
+            rows, keep = to_gpu_rows(x, offset)
+            hv.hvdx_ring_allreduce_whole([r.data_ptr() for r in rows], n, x.shape[1], NP_TO_HV[x.dtype], hv.AVERAGE,
+                                         hv.COMPRESS_FP16 if compress else hv.COMPRESS_NONE,
+                                         torch.cuda.current_stream().cuda_stream)
+            assert_bits_equal(from_gpu_rows(rows), oracle_ring(x, "average", compress), f"flat offset={offset}")
+        for layout in ("packed", "unalike"):
+            host, dev = rank_lists(rng, n, numel, dtype, layout)
+            hv.FusedAllreduce(dev, compress=compress, threshold_bytes=2000)()
+            torch.cuda.synchronize()
+            want = native.allreduce(host, "average", compress=compress, threshold=2000)
+            for r in range(n):
+                for t in range(len(numel)):
+                    assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"{layout} rank {r} tensor {t}")
 
 
 def rank_lists(rng, n, numel, dtype, layout):

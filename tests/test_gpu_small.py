@@ -100,22 +100,28 @@ def test_fuse_allreduce_small_matches_oracle(case, misalign):
             assert_bits_equal(dev[r][t].cpu().numpy(), want[t], f"rank {r} tensor {t}")
 
 
-@pytest.mark.parametrize("small_bytes", [0, hv.SMALL_BUCKET_BYTES, 1 << 40], ids=["per-step", "default", "all"])
-def test_fused_allreduce_picks_either_path_with_the_same_bits(small_bytes):
-    """Mixed plan (fused buckets, direct tensors, compression) through FusedAllreduce
-    with no, the default, and every bucket on the one-launch path."""
-    numel = [3000, 1, 2, 50000, 64, 64, 64, 128 * 1024, 9, 7]
-    for compress in (False, True):
+@pytest.mark.parametrize("small_bytes,kinds", [
+    (0, {"rs", "rs_ag", "ag"}),  # no bucket in one launch
+    (1100, {"rs", "rs_ag", "ag", "cycle_small", "ring_small"}),  # the small ones of each kind, in kernels of their own
+    (hv.SMALL_BUCKET_BYTES, {"cycle_small", "ring_small"}),  # the default: all of them, over a table
+], ids=["per-step", "some", "default"])
+def test_fused_allreduce_picks_either_path_with_the_same_bits(small_bytes, kinds):
+    """Mixed plan (fused buckets, direct tensors, compression) through FusedAllreduce with none,
+    some and every bucket on a one-launch path."""
+    numel = [3000, 1, 2, 50000, 64, 64, 64, 128 * 1024, 9, 7, 11000, 100]
+    for threshold, compress in ((40000, False), (40000, True), (900, False)):
         rng = np.random.default_rng(220)
         host, dev, keep = make_tensors(rng, 6, numel, np.float32)
-        say(f"FusedAllreduce small_bucket_bytes={small_bytes} compress={compress}")
-        ar = hv.FusedAllreduce(dev, op="average", compress=compress, threshold_bytes=40000,
-                               small_bucket_bytes=small_bytes)
-        kinds = {k for k, _, _ in ar.kernel_sequence()}
-        assert ("cycle_small" in kinds) == (small_bytes > 0)
+        say(f"FusedAllreduce small_bucket_bytes={small_bytes} threshold={threshold} compress={compress}")
+        ar = hv.FusedAllreduce(dev, op="average", compress=compress, threshold_bytes=threshold,
+                               small_bucket_bytes=small_bytes, pair_buckets=small_bytes >= hv.SMALL_BUCKET_BYTES)
+        got = {k for k, _, _ in ar.kernel_sequence()}
+        assert got <= kinds and ("cycle_small" in got) == ("cycle_small" in kinds)
+        if threshold == 900 and "rs" in kinds and small_bytes:
+            assert "rs" in got  # direct tensors in steps beside the small buckets
         ar()
         torch.cuda.synchronize()
-        want = allreduce.allreduce(host, "average", compress=compress, threshold=40000)
+        want = allreduce.allreduce(host, "average", compress=compress, threshold=threshold)
         for r in range(6):
             for t in range(len(numel)):
                 assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")

@@ -187,11 +187,65 @@ def test_small_cycle_one_thread_per_element():
                 assert (owner[inside] >= 0).all()
 
 
-def test_one_launch_ring_and_fold_one_thread_per_element():
+def test_one_launch_ring_on_flat_buffers():
     for count in (1, 3, 4, 5, 1001, 65536 * 4 + 7, 256 * 4 * 3 + 1):
-        assert (W.chain_threads(count, 4, 3) == 1).all()
-        assert (W.chain_threads(count, 8, 5) == 1).all()
-        assert (W.chain_threads(count, 4, 5, fold=True) == 1).all()
+        for V, n in ((4, 3), (8, 5), (4, 8)):
+            hits, loads = W.fold_flat(count, V, n)
+            assert (hits == 1).all() and (loads >= 1).all()
+
+
+@pytest.mark.parametrize("esizes", [(4, 4), (4, 2), (2, 2)], ids=["f32", "f32-to-f16", "f16"])
+def test_one_launch_ring_over_a_table(esizes):
+    """Every element of every tensor stored by one lane, which loaded it, and nothing outside the
+    tensors touched, over the tables the library cuts: narrow tiles with their heads, and wide ones."""
+    import paper_1802_05799_amd as hv
+    from test_fold_table import LAYOUTS, addresses, read_table
+
+    te, be = esizes
+    dt = {4: hv.FLOAT32, 2: hv.FLOAT16}
+    seen = set()
+    for numel, n, threshold in (([7, 64, 100, 1000, 4608, 513], 3, 64 << 20), ([0, 3, 0, 5], 8, 0),
+                                ([2048 * 3, 5, 4096 * 2 + 3, 1, 9000], 5, 4096), ([140_003, 9], 2, 64 << 20)):
+        for layout in LAYOUTS:
+            bucket_of, offset, counts, _ = hv.hvdx_fuse_plan(numel, dt[be], threshold)
+            ptrs = addresses(numel, n, te, layout)
+            table, ntiles, stretches = hv.hvdx_fuse_cycle_table(ptrs, numel, offset, bucket_of, counts, dt[te], dt[be], n)
+            _, tiles = read_table(table, len(numel), n, ntiles)
+            w, r = W.fold_table(numel, tiles, stretches, 16 // te)
+            assert all((x == 1).all() for x in w) and all((x >= 1).all() for x in r), (numel[:3], n, layout)
+            seen.add(stretches)
+            if layout == "packed" and numel[0] == 2048 * 3:
+                for bad in (W.Knobs(lane_shift=1), W.Knobs(edge_lanes_short=1)):
+                    with pytest.raises((AssertionError, IndexError)):
+                        w, _ = W.fold_table(numel, tiles, stretches, 16 // te, bad)
+                        assert all((x == 1).all() for x in w)
+            if stretches > 1:
+                w, _ = W.fold_table(numel, tiles, stretches, 16 // te, W.Knobs(part_shift=-16 // te))
+                assert not all((x == 1).all() for x in w)
+    assert seen == {1, 4}
+
+
+def test_bursts_stay_inside_the_pointer_lists():
+    """A burst reads pointers past its ring's last rank (and uses none): from any first rank on they
+    lie in the list of 2n and the pad after it.  The GPU tests run every burst there is."""
+    for n in range(1, 129):
+        B = W.fold_burst(n)
+        assert 2 <= B <= 16
+        left = n % B
+        reads = n + (B - left if left else 0)  # per ring: whole bursts, the last one whole too
+        assert (n - 1) + reads <= 2 * n + W.FOLD_PAD
+    assert {W.fold_burst(n) for n in W.BURST_RANKS} == set(range(2, 17)) == {W.fold_burst(n) for n in range(1, 129)}
+
+
+@pytest.mark.parametrize("U", [1, 2, 4])
+def test_whole_broadcast_stores_every_byte(U):
+    for nbytes in (1, 15, 16, 17, 31, 1023, 1024, 1025, 2048 * 3 + 5, 4096 * 2 - 1):
+        for address in (0, 5, 16, 100, 4095):
+            assert (W.bcast_whole(nbytes, address, U) >= 1).all()
+    with pytest.raises((AssertionError, IndexError)):
+        assert (W.bcast_whole(1023, 0, U, W.Knobs(clamp_tail=False)) >= 1).all()
+    with pytest.raises((AssertionError, IndexError)):
+        assert (W.bcast_whole(1024, 0, U, W.Knobs(lane_shift=1)) >= 1).all()
 
 
 def test_broadcast_steps():

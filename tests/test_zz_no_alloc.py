@@ -1,8 +1,7 @@
-"""hvdx_ring_allreduce_noalloc (the ring whose compression workspace is a static array
-inside the library) against hvdx_ring_allreduce with a caller's workspace: the same
-bits, through the C-ABI, on calls in a row (each smaller than the one before, so a call
-runs over the array as the previous one left it), compressed and not, and a request
-past the array's size refused."""
+"""hvdx_ring_allreduce_noalloc and hvdx_ring_allreduce_whole (the ring in one launch without a
+workspace argument) against hvdx_ring_allreduce_steps (other kernels: a launch per step, the
+messages through memory and, compressed, through a caller's workspace): the same bits, through
+the C-ABI, on calls in a row, compressed and not, and the former's limit refused."""
 import numpy as np
 import pytest
 import torch
@@ -17,35 +16,35 @@ def rows(x):
     return [torch.from_numpy(np.ascontiguousarray(r)).cuda() for r in x]
 
 
-def with_workspace(x, op, compress):
+def in_steps(x, op, compress):
     n, count = x.shape
     r = rows(x)
     wsb = hv.hvdx_ring_workspace_bytes(n, count, hv.FLOAT32, compress)
     ws = torch.empty(max(wsb, 1), dtype=torch.uint8, device="cuda")
-    hv.hvdx_ring_allreduce([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress, ws.data_ptr() if wsb else 0,
-                           wsb, torch.cuda.current_stream().cuda_stream)
+    hv.hvdx_ring_allreduce_steps([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress,
+                                 ws.data_ptr() if wsb else 0, wsb, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return np.stack([t.cpu().numpy() for t in r])
 
 
-def without_workspace(x, op, compress):
+def without_workspace(call, x, op, compress):
     n, count = x.shape
     r = rows(x)
-    hv.hvdx_ring_allreduce_noalloc([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress,
-                                   torch.cuda.current_stream().cuda_stream)
+    call([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return np.stack([t.cpu().numpy() for t in r])
 
 
-CALLS = [  # (ranks, elements) of consecutive calls; the first fills most of the 64 MiB array
-    (8, 4_194_304 - 128),  # 8 x 4,194,176 binary16 wire elements = 64 MiB - 2 KiB
+CALLS = [  # (ranks, elements) of consecutive calls; the first just under the 64 MiB limit
+    (8, 4_194_304 - 128),  # 8 x 4,194,176 binary16 elements = 64 MiB - 2 KiB
     (5, 100_003),  # not a power of two: a true division; chunks not 16-byte aligned
     (3, 1_001),
+    (1, 4_099),  # one rank: rounded to binary16 when compressed
 ]
 
 
 @pytest.mark.parametrize("compress", [hv.COMPRESS_FP16, hv.COMPRESS_NONE], ids=["fp16-wire", "no-compression"])
-def test_noalloc_matches_workspace_entry_point(compress):
+def test_noalloc_matches_the_ring_in_steps(compress):
     assert hv.hvdx_ring_noalloc_max_bytes() == 64 << 20
     rng = np.random.default_rng(2024)
     for k, (n, count) in enumerate(CALLS):
@@ -53,14 +52,15 @@ def test_noalloc_matches_workspace_entry_point(compress):
             say(f"noalloc call {k}: N={n} count={count} op={op} compress={compress}")
             x = (rng.standard_normal((n, count)) * 0.01).astype(np.float32)
             x[:, :6] = np.array([0.0, -0.0, 2.0 ** -24, 65504.0, 1e-8, -3.0], np.float32)
-            want = with_workspace(x, op, compress)
-            got = without_workspace(x, op, compress)
-            assert_bits_equal(got, want, f"call {k} N={n} count={count} op={op}")
-            assert all(np.array_equal(got[r].view(np.uint32), got[0].view(np.uint32)) for r in range(n))
+            want = in_steps(x, op, compress)
+            assert all(np.array_equal(want[r].view(np.uint32), want[0].view(np.uint32)) for r in range(n))
+            for call in (hv.hvdx_ring_allreduce_noalloc, hv.hvdx_ring_allreduce_whole):
+                got = without_workspace(call, x, op, compress)
+                assert_bits_equal(got, want, f"{call.__name__} call {k} N={n} count={count} op={op}")
 
 
-def test_noalloc_refuses_more_than_the_static_array():
-    n, count = 8, 4_194_304 + 1  # one element past the 64 MiB of binary16 wire copies
+def test_noalloc_refuses_more_than_its_limit():
+    n, count = 8, 4_194_304 + 1  # one element past 64 MiB in binary16
     assert hv.hvdx_ring_workspace_bytes(n, count, hv.FLOAT32, hv.COMPRESS_FP16) > hv.hvdx_ring_noalloc_max_bytes()
     x = [torch.zeros(count, device="cuda") for _ in range(n)]
     with pytest.raises(hv.HvdxError) as e:
