@@ -547,9 +547,10 @@ int hvdx_broadcast_tensors_step(const void* const* ptrs, const int64_t* nbytes, 
  * computed without the ring's messages: each element's N values are read once and
  * added in the ring's order (starting at the rank whose chunk holds the element,
  * paper section 3), divided once for AVERAGE, and written to all N buffers.  It
- * moves 2N elements per element instead of the ring's 5(N-1), so it bounds what a
- * one-GPU schedule can do; it is not a simulation of the ring's transport.  The kernel
- * is hvdx_ring_allreduce_small's, which this call offers compressed too.
+ * moves 2N elements per element instead of the 5(N-1) of a launch per step, so it bounds
+ * what a one-GPU schedule can do; it is not a simulation of the ring's transport.  The
+ * kernel is hvdx_ring_allreduce_whole's, with cached loads where the buffers fit the
+ * Infinity Cache: faster on repeated calls, slower on buffers no cache holds.
  * Arguments as hvdx_ring_allreduce; compression needs no workspace here.
  */
 int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress, void* stream);

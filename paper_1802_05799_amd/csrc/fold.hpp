@@ -111,11 +111,17 @@ __device__ __forceinline__ T* uniform_here(T* p) {
   return reinterpret_cast<T*>((uint64_t)hi << 32 | lo);
 }
 
+template <bool CACHED, typename P>
+__device__ __forceinline__ auto fold_load(P p) {
+  if constexpr (CACHED) return *p;
+  else return __builtin_nontemporal_load(p);
+}
+
 // One vector per lane.  ptr(k) is the address of the stretch's first element on the k-th
 // rank of its ring (rank c+k mod N).  The last burst reads, but does not use, up to ptr(n+B-2):
 // with the ring's ranks from rank c on, entry c+n+B-2 <= 2n+B-3 of a list of 2n; MT is
 // FoldTypes::vec or, unaligned, ::uvec.
-template <typename TT, typename TB, int B, typename MT, typename Ptr>
+template <typename TT, typename TB, bool CACHED, int B, typename MT, typename Ptr>
 __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, int mode) {
   static_assert(B - 2 <= kFoldPad, "a list of 2n rank pointers is followed by kFoldPad more");
   using F = FoldTypes<TT, TB>;
@@ -129,7 +135,7 @@ __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, 
   for (; k0 + B <= n; k0 += B) {  // whole bursts, no test between the loads
     vec x[B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) x[j] = __builtin_nontemporal_load(at(ptr(k0 + j)));
+    for (int j = 0; j < B; ++j) x[j] = fold_load<CACHED>(at(ptr(k0 + j)));
     __builtin_amdgcn_sched_barrier(0);  // no addition, and so no wait, before the last load is out
 #pragma unroll
     for (int j = 0; j < B; ++j) s = F::in(x[j]) + s;
@@ -142,7 +148,7 @@ __device__ __forceinline__ void fold_vectors(const Ptr& ptr, const RingArgs& a, 
     for (int j = 0; j < B; ++j) p[j] = uniform_here(ptr(k0 + j));
 #pragma unroll
     for (int j = 0; j < B; ++j)
-      if (j < left) x[j] = __builtin_nontemporal_load(at(p[j]));
+      if (j < left) x[j] = fold_load<CACHED>(at(p[j]));
 #pragma unroll
     for (int j = 0; j < B; ++j)
       if (j < adds) s = F::in(x[j]) + s;
@@ -181,7 +187,7 @@ __device__ __forceinline__ void fold_element(const Ptr& ptr, const RingArgs& a, 
 // 16-byte boundary in a wavefront of its own, Inception-V3's tensors reduced one by one on 16 ranks
 // 565 us, 510 so).  Lanes past the last vector or element
 // load that one too, and store nothing.
-template <typename TT, typename TB, int B, typename MT, typename Ptr>
+template <typename TT, typename TB, bool CACHED, int B, typename MT, typename Ptr>
 __device__ __forceinline__ void fold_edges(const Ptr& ptr, const RingArgs& a, int mode, int head, int vecs, int rest) {
   using F = FoldTypes<TT, TB>;
   const int n = a.n, lane = threadIdx.x;
@@ -199,7 +205,7 @@ __device__ __forceinline__ void fold_edges(const Ptr& ptr, const RingArgs& a, in
 #pragma unroll
     for (int j = 0; j < B; ++j) {
       TT* p = ptr(k0 + j < n ? k0 + j : n - 1);
-      x[j] = __builtin_nontemporal_load(vector(p));
+      x[j] = fold_load<CACHED>(vector(p));
       y[j] = *element(p);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -224,7 +230,7 @@ __device__ __forceinline__ void fold_edges(const Ptr& ptr, const RingArgs& a, in
 
 // A wavefront's stretch of m (1 .. 64*V) elements; aligned: its element `head` (< V) lies on a
 // 16-byte boundary of every rank (head is 0 if not).
-template <typename TT, typename TB, int B, typename Ptr>
+template <typename TT, typename TB, bool CACHED, int B, typename Ptr>
 __device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, int mode, int m, bool aligned,
                                              int head) {
   using F = FoldTypes<TT, TB>;
@@ -232,11 +238,11 @@ __device__ __forceinline__ void fold_stretch(const Ptr& ptr, const RingArgs& a, 
   if (head > m) head = m;
   const int vecs = (m - head) / F::V, rest = m - vecs * F::V;
   if (vecs && rest) {
-    if (aligned) fold_edges<TT, TB, B, typename F::vec>(ptr, a, mode, head, vecs, rest);
-    else fold_edges<TT, TB, B, typename F::uvec>(ptr, a, mode, head, vecs, rest);
+    if (aligned) fold_edges<TT, TB, CACHED, B, typename F::vec>(ptr, a, mode, head, vecs, rest);
+    else fold_edges<TT, TB, CACHED, B, typename F::uvec>(ptr, a, mode, head, vecs, rest);
   } else if (lane < vecs) {
-    if (aligned) fold_vectors<TT, TB, B, typename F::vec>(ptr, a, mode);
-    else fold_vectors<TT, TB, B, typename F::uvec>(ptr, a, mode);
+    if (aligned) fold_vectors<TT, TB, CACHED, B, typename F::vec>(ptr, a, mode);
+    else fold_vectors<TT, TB, CACHED, B, typename F::uvec>(ptr, a, mode);
   } else if (lane < rest) {
     fold_element<TT, TB>(ptr, a, mode, lane);
   }

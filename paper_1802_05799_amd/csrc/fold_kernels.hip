@@ -16,11 +16,21 @@ namespace {
 // rank pointers are listed twice over, so that a ring's ranks from any first rank on are one
 // run of them (scalar loads, several per instruction).
 
+// Loads are non-temporal: nothing read is read again, and a launch on data that no cache holds is
+// 5 to 15% faster so.  Cached ones keep data that fits the Infinity Cache in it from one call on
+// the same buffers to the next; on buffers another kernel has just written the two are alike (us,
+// non-temporal and cached, 128 MiB in all: on 2 ranks repeated 42.3 and 32.8, from memory 43.2 and
+// 49.2, just written 44.0 and 42.3; on 8 ranks 47.3 and 37.3, 49.0 and 51.9, 42.6 and 42.6).  So a
+// caller can ask for them (`cached`): hvdx_fold_allreduce and the ring of 2 ranks, which were one
+// launch with cached loads before all rings were, and would lose on repeated calls.  Up to a
+// little over the cache's 256 MiB (2 ranks, 272 MiB: 88.1 and 74.9, 304: 98.1 and 103.5).
+constexpr int64_t kCachedBytes = 272ll << 20;
+
 struct RingPtrs {
   void* p[2 * HVDX_MAX_RANKS + kFoldPad];
 };
 
-template <typename TT, typename TB, int B>
+template <typename TT, typename TB, bool CACHED, int B>
 __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(RingPtrs bufs, RingArgs a, int mode, bool aligned) {
   constexpr int64_t S = kFoldLanes * FoldTypes<TT, TB>::V;
   const int c = blockIdx.y;
@@ -31,7 +41,7 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_flat_kernel(Ri
     const int64_t e1 = (g + 1) * S < end ? (g + 1) * S : end;
     auto ptr = [&](int k) { return static_cast<TT*>(bufs.p[c + k]) + e0; };
     const bool al = aligned && e0 % FoldTypes<TT, TB>::V == 0;
-    fold_stretch<TT, TB, B>(ptr, a, mode, (int)(e1 - e0), al, 0);
+    fold_stretch<TT, TB, CACHED, B>(ptr, a, mode, (int)(e1 - e0), al, 0);
   }
 }
 
@@ -60,7 +70,7 @@ __global__ __launch_bounds__(kFoldLanes, fold_waves(B)) void fold_table_kernel(F
   if (left <= 0) return;
   const int64_t li = ((int64_t)w[1] << 32 | (uint32_t)w[0]) + part;
   auto ptr = [&](int k) { return static_cast<TT*>(p[k]) + li; };
-  fold_stretch<TT, TB, B>(ptr, a, mode, left < S ? left : S, bits >> 24 & 1, (int)(bits >> 28));
+  fold_stretch<TT, TB, false, B>(ptr, a, mode, left < S ? left : S, bits >> 24 & 1, (int)(bits >> 28));
 }
 
 // Whether to hold the wavefronts per CU down (fold_lds).  Not in a launch so short that filling the
@@ -97,7 +107,7 @@ void with_types(int tensor_dtype, int buf_dtype, int burst, const F& f) {
 }  // namespace
 
 hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
-                            bool aligned, hipStream_t stream) {
+                            bool aligned, bool cached, hipStream_t stream) {
   if (a.n == 1 && tensor_dtype == buf_dtype) return hipSuccess;  // the buffer is its own sum
   const int64_t span = kFoldLanes * (tensor_dtype == HVDX_FLOAT16 ? 8 : 4);
   int64_t bx = (a.q + (a.rem ? 1 : 0)) / span + 2;  // a chunk may begin and end inside a stretch
@@ -107,9 +117,15 @@ hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_
   const unsigned lds = fold_holds(bx * a.n, a.q * a.n + a.rem, a.n, tensor_dtype) ? fold_lds(a.n, burst) : 0;
   RingPtrs ptrs{};  // the pad is read, if not used
   for (int r = 0; r < a.n; ++r) ptrs.p[r] = ptrs.p[a.n + r] = bufs.p[r];
+  const int64_t bytes = (a.q * a.n + a.rem) * a.n * (tensor_dtype == HVDX_FLOAT16 ? 2 : 4);
+  cached = cached && bytes <= kCachedBytes;
   with_types(tensor_dtype, buf_dtype, burst, [&](auto tt, auto tb, auto b) {
-    HVDX_LAUNCH((fold_flat_kernel<decltype(tt), decltype(tb), b.value>), grid, dim3(kFoldLanes), lds, stream, ptrs, a,
-                divmode, aligned);
+    if (cached)
+      HVDX_LAUNCH((fold_flat_kernel<decltype(tt), decltype(tb), true, b.value>), grid, dim3(kFoldLanes), lds, stream,
+                  ptrs, a, divmode, aligned);
+    else
+      HVDX_LAUNCH((fold_flat_kernel<decltype(tt), decltype(tb), false, b.value>), grid, dim3(kFoldLanes), lds, stream,
+                  ptrs, a, divmode, aligned);
   });
   return hipGetLastError();
 }

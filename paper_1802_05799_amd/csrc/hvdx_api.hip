@@ -561,7 +561,7 @@ static int run_whole_ring(void* const* bufs, int nranks, int64_t count, int dtyp
   TimedLaunch timed_phase(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, compress, count, st, -1, true);
   const hipError_t e = hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), dtype,
                                               compress == HVDX_COMPRESS_FP16 ? HVDX_FLOAT16 : dtype,
-                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
+                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), nranks == 2, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "one-launch ring");
 }
 
@@ -1143,7 +1143,7 @@ int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   TimedLaunch timed_phase(HVDX_KERNEL_FOLD, -1, nranks, dtype, compress, count, st, -1, true);
   const hipError_t e =
       hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), a, dtype, compress == HVDX_COMPRESS_FP16 ? HVDX_FLOAT16 : dtype,
-                             div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), st);
+                             div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), true, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "fold launch");
 }
 

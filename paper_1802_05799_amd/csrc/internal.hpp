@@ -142,9 +142,10 @@ hipError_t launch_small_cycle(const void* const* tensors, const int64_t* numel, 
                               hipStream_t stream);
 
 // The whole ring in one launch (fold_kernels.hip): each lane runs every step for its elements,
-// the messages in registers.  Over flat rank buffers (a holds their partition):
+// the messages in registers.  Over flat rank buffers (a holds their partition), with cached loads
+// where asked for and the buffers fit the Infinity Cache:
 hipError_t launch_fold_flat(const RankPtrs& bufs, const RingArgs& a, int tensor_dtype, int buf_dtype, int divmode,
-                            bool aligned, hipStream_t stream);
+                            bool aligned, bool cached, hipStream_t stream);
 // ... and over the tensors of a table, where a tile is at most 64 16-byte vectors of one tensor in one
 // ring chunk, a wavefront's stretch, or kFoldWide times that.  Wide tiles leave blocks with nothing
 // to do at each piece's end, and need a tile of its own for what precedes a piece's first 16-byte

@@ -154,6 +154,24 @@ def test_steps_of_a_one_launch_object():
                     assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
 
 
+@pytest.mark.parametrize("n", [2, 5])
+def test_cached_and_streamed_loads(n):
+    """hvdx_fold_allreduce, and the ring on 2 ranks, load through the caches up to 272 MiB in all:
+    either side of it, against the ring in steps."""
+    for count in ((272 << 18) // n, (272 << 18) // n + 1000):
+        say(f"cached and streamed loads n={n} count={count}")
+        g = torch.Generator(device="cuda").manual_seed(n)
+        want = [torch.empty(count, device="cuda").normal_(0.0, 0.01, generator=g) for _ in range(n)]
+        rows = [[x.clone() for x in want] for _ in range(2)]
+        s = torch.cuda.current_stream().cuda_stream
+        hv.hvdx_ring_allreduce_steps([x.data_ptr() for x in want], n, count, hv.FLOAT32, hv.AVERAGE, 0, 0, 0, s)
+        hv.hvdx_fold_allreduce([x.data_ptr() for x in rows[0]], n, count, hv.FLOAT32, hv.AVERAGE, 0, s)
+        hv.hvdx_ring_allreduce([x.data_ptr() for x in rows[1]], n, count, hv.FLOAT32, hv.AVERAGE, 0, 0, 0, s)
+        torch.cuda.synchronize()
+        for got in rows:
+            assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(got, want))
+
+
 ALONE_CASES = [
     # (numel, ranks, threshold, binary16 tensors, compress, elements off a 16-byte start, launches without a table)
     ([17_000_001], 2, 64 << 20, False, False, 0, [0]),  # above 64 MiB a rank
