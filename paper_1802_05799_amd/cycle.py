@@ -3,30 +3,30 @@
 `FusedAllreduce` is built once for a fixed set of gradient tensors (one list per
 simulated rank, all in GPU memory) and then reduces them in place each time it is
 called: every fusion buffer of the plan goes through the ring-allreduce of paper
-section 3; a tensor larger than the buffer runs the ring in place on the rank tensors
-themselves.  By default a fusion buffer's ring runs on the ranks' tensors: its adding
-steps read each rank's own elements from the tensors (where a copy-in would take them
-from), the buffers hold the partial sums received, and its replacing steps write the
-tensors (where a copy-out would put them); the paper's copies are options.  Torch
-provides the device memory and the stream; every step is a libhvdx kernel.
+section 3; a tensor larger than the buffer runs the ring by itself.  Torch provides the
+device memory and the stream; every step is a libhvdx kernel.
 
-The fusion buffers are allocated once, at the size of the largest fused bucket
-(at most the threshold, 64 MiB by default), and reused for every bucket, as the
-paper's step 2 describes.  The descriptor arrays the kernels read (tensor pointers,
-sizes, offsets, tile tables) are uploaded once at construction, so the tensors must
-stay allocated and in place for the object's lifetime.
+By default a call is one launch for all fusion buffers and one for the tensors reduced by
+themselves (hvdx_fuse_cycle; few ranks' large ones in launches of their own,
+hvdx_ring_allreduce_whole): each lane takes its elements through all 2(N-1) steps of the
+ring in their order, straight on the ranks' tensors, the messages in registers, so an
+element is read once and written once per rank, 2N elements moved instead of the 5N-6 of a
+launch per step (VGG-16 on 32 ranks: 12.9 ms in steps, 6.0 ms in one launch).  No fusion
+buffer exists then; a table of the tensors' stretches is cut and uploaded once, so the
+tensors must stay allocated and in place for the object's lifetime.
 
-By default all of that runs in one launch for every fusion buffer and one for every tensor
-reduced by itself (hvdx_fuse_cycle): each lane takes its elements through all 2(N-1)
-steps of the ring in their order, the messages in registers, so an element is read once
-and written once per rank, 2N elements moved instead of the 5N-6 of a launch per step
-(VGG-16 on 32 ranks: 12.9 ms in steps, 6.0 ms in one launch).  An argument that asks for
-the steps themselves (see FusedAllreduce) gets a launch, and a timeline record, per step;
-buckets of at most `small_bucket_bytes` per rank then still run in one launch
-(hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small).  Fused buckets on the per-step path
-run in groups, in plan order, every launch serving the whole group (up to four
-buffers with the ring on the tensors, else two), each member after the first with
-fusion buffers of its own.  Same bits either way.
+An argument that asks for the steps themselves (see FusedAllreduce) gets a launch, and a
+timeline record, per step.  The fusion buffers are then allocated once, at the size of the
+largest fused bucket (at most the threshold, 64 MiB by default), and reused for every
+bucket, as the paper's step 2 describes; a default object allocates them when a step of it
+is first asked for.  A fusion buffer's ring runs on the ranks' tensors: its adding steps read
+each rank's own elements from the tensors (where a copy-in would take them from), the buffers
+hold the partial sums received, and its replacing steps write the tensors (where a copy-out
+would put them); the paper's copies are options.  Buckets of at most `small_bucket_bytes` per
+rank still run in one launch (hvdx_fuse_allreduce_small, hvdx_ring_allreduce_small).  The
+other fused buckets run in groups, in plan order, every launch serving the whole group (up to
+four buffers with the ring on the tensors, else two), each member after the first with fusion
+buffers of its own.  Same bits either way.
 """
 from __future__ import annotations
 
@@ -97,7 +97,12 @@ class FusedAllreduce:
                  schedule: str = "ring", fuse_boundary: bool = True,
                  small_bucket_bytes: int = L.SMALL_BUCKET_BYTES, pair_buckets: bool = True, tiled: bool = True,
                  replace_in_tensors: bool = True, add_from_tensors: bool = True):
-        """schedule "ring" runs the ring's 2(N-1) steps; "fold" computes the same bits
+        """With every argument after align_bytes at its default (small_bucket_bytes at 4 MiB or
+        more) and two ranks or more, a call is one launch for all fusion buffers and one for the
+        direct tensors, whatever their sizes.  Any other value takes the per-step path, which
+        the rest of this text is about (small_bucket_bytes=0 alone: the ring on the tensors, a
+        launch per step).
+        schedule "ring" runs the ring's 2(N-1) steps; "fold" computes the same bits
         with hvdx_fold_allreduce (no per-step messages: a one-GPU bound, not the ring).
         With fuse_boundary (ring schedule, N >= 3) a fusion buffer's copy-in runs with
         the ring's first adding step and its copy-out with the last replacing step
@@ -368,7 +373,8 @@ class FusedAllreduce:
         deliver into the tensors and no copy-out follows; with the adding steps from the
         tensors, "rs" 0..N-3 replace "pack_rs"), "unpack", "fold", "ring"
         (the one-rank compressed round trip),
-        "cycle_small" or "ring_small" (a small bucket's whole cycle in one launch).
+        "cycle_small" or "ring_small" (whole cycles of fusion buffers or of direct tensors in one
+        launch).
         A launch that serves a group of buckets names them all: (kind, (i, j, ...), step)."""
         if self._cycles is not None:
             return [(c.kind, c.members if len(c.members) > 1 else c.members[0], -1) for c in self._cycles]
@@ -421,13 +427,13 @@ class FusedAllreduce:
         return out + [("ag", bi, s) for s in range(1, n - 2)] + [("ag_unpack", bi, n - 2)]
 
     def capture(self) -> "torch.cuda.CUDAGraph":
-        """Record one call's launches (every bucket's copy-in, ring steps and copy-out)
-        in a HIP graph and return it without running them.  ``graph.replay()`` then
-        reduces the same tensors, in place, with one submission instead of one launch
-        per kernel, which is what decides the time of small buckets.  The tensors,
-        fusion buffers and descriptors the graph points at are this object's; the graph
-        holds a reference to it.  Launches inside the capture get no
-        timeline records."""
+        """Record one call's launches in a HIP graph and return it without running them.
+        ``graph.replay()`` then reduces the same tensors, in place, with one submission instead
+        of one launch per kernel: less time where a call has many (ResNet-50's 161 tensors one by
+        one in steps 8.8 and 5.8 ms), more where it has one or two, as by default (a toy list's 4
+        us, 12 to 17 replayed).  The tensors, fusion buffers and descriptors the graph points at
+        are this object's; the graph holds a reference to it.  Launches inside the capture get
+        no timeline records."""
         graph = torch.cuda.CUDAGraph()
         side = torch.cuda.Stream(self.device)  # default priority
         side.wait_stream(torch.cuda.current_stream(self.device))
