@@ -382,6 +382,9 @@ def short_kernel_name(full):
         return "cycle_small"
     if "fold_table_kernel" in base or "fold_flat_kernel" in base:
         return "whole_ring"
+    for key, short in (("bcast_tensors_kernel", "broadcast_list"), ("bcast_kernel", "broadcast_flat")):
+        if key in base:  # the whole chain in one launch
+            return short
     # the tile-driven ring steps report as the ring step they are; binary32 tensors with
     # binary16 buffers are the compressed ring's (its replacing steps copy binary32)
     mixed = re.search(r"tiles_kernel<float, _Float16", base) or re.search(r"tiles_kernelIfDF16_", base)
@@ -420,6 +423,9 @@ def shape_of(full):
     if "tiles_kernel" in full:  # the vectors per lane: the last template argument
         m = re.search(r"tiles_kernel<[^>]*,\s*(\d+)>", full) or re.search(r"tiles_kernelI.*Li(\d+)EEEv", full)
         return f"tiles<{m.group(1)}>" if m else "tiles"
+    m = re.search(r"bcast_(?:tensors_)?kernel(?:<|ILi)(\d+)[>E]", full)
+    if m:
+        return f"{m.group(1)} units per lane"
     m = re.search(r"fold_(table|flat)_kernel(?:<[^>]*,\s*|I.*Li)(\d+)[>E]", full)
     if m:
         return f"{m.group(1)}, bursts of {m.group(2)}"

@@ -164,6 +164,14 @@ REAL_NAMES = {
     "_ZN4hvdx12_GLOBAL__N_116add_tiles_kernelIfDF16_Lb0ELi2ELi2EEEvNS_9TiledCopyEiil": ("rs_step_c16", "tiles<2>"),
     "_ZN4hvdx12_GLOBAL__N_118rs_ag_tiles_kernelIfDF16_Li2ELb1ELi2EEEvNS_9TiledCopyENS_8RingArgsE":
         ("rs_ag_step_c16", "tiles<2>"),
+    "void hvdx::(anonymous namespace)::fold_flat_kernel<float, float, true, 4>(hvdx::(anonymous namespace)::RingPtrs, "
+    "hvdx::RingArgs, int, bool)": ("whole_ring", "flat, bursts of 4"),
+    "_ZN4hvdx12_GLOBAL__N_117fold_table_kernelIfDF16_Li16EEEvNS_9FoldTableENS_8RingArgsEi":
+        ("whole_ring", "table, bursts of 16"),
+    "void hvdx::(anonymous namespace)::bcast_tensors_kernel<2>(hvdx::BcastTensorsArgs)":
+        ("broadcast_list", "2 units per lane"),
+    "void hvdx::(anonymous namespace)::bcast_kernel<4>(hvdx::RankPtrs, hvdx::BcastArgs, int)":
+        ("broadcast_flat", "4 units per lane"),
     "__amd_rocclr_copyBuffer": (None, ""),
 }
 
