@@ -410,7 +410,11 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
  * hvdx_ring_allreduce runs all of it in one launch: an element's ring never involves another
  * element, so a lane takes its elements through every step, the messages in registers (2N
  * elements moved per element; the workspace is checked but not used).
- * hvdx_ring_allreduce_whole is that without a workspace argument, compressed or not.
+ * hvdx_ring_allreduce_whole is that without a workspace argument, compressed or not, and
+ * with a say in how the buffers are loaded: `cached` 1 through the caches (up to 272 MiB of
+ * all ranks' bytes, else as 0), faster where they are still in the Infinity Cache from a call
+ * before, or 0 non-temporally, faster where they are not.  The other calls do the former on
+ * 2 ranks, the latter on more.
  * hvdx_ring_allreduce_steps runs a launch per step, the messages through the buffers (and the
  * workspace), for tracing: every step then has its record in a timeline.  (Adding step N-2
  * and replacing step 0 run as one kernel there; the buffers end the same.)  Same bits.
@@ -419,7 +423,7 @@ int hvdx_fuse_allreduce_small(void* const* tensors, const int64_t* numel, const 
 int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                         void* workspace, size_t workspace_bytes, void* stream);
 int hvdx_ring_allreduce_whole(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
-                              void* stream);
+                              int cached, void* stream);
 int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
                               void* workspace, size_t workspace_bytes, void* stream);
 

@@ -47,7 +47,7 @@ _SIGNATURES = {
     "hvdx_fuse_cycle_table": (_i64, [_p, _p, _p, _p, _p, _i, _i, _i, _i, _i, _p, _i64, _pi64, ctypes.POINTER(_i)]),
     "hvdx_fuse_cycle": (_i, [_p, _i, _i64, _i, _i64, _i, _i, _i, _i, _i, _p]),
     "hvdx_ring_allreduce": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
-    "hvdx_ring_allreduce_whole": (_i, [_pp, _i, _i64, _i, _i, _i, _p]),
+    "hvdx_ring_allreduce_whole": (_i, [_pp, _i, _i64, _i, _i, _i, _i, _p]),
     "hvdx_ring_allreduce_steps": (_i, [_pp, _i, _i64, _i, _i, _i, _p, _sz, _p]),
     "hvdx_ring_allreduce_small": (_i, [_pp, _i, _i64, _i, _i, _p]),
     "hvdx_ring_allreduce_noalloc": (_i, [_pp, _i, _i64, _i, _i, _i, _p]),
@@ -343,9 +343,9 @@ def hvdx_ring_allreduce(bufs, nranks: int, count: int, dtype: int, op: int, comp
 
 
 def hvdx_ring_allreduce_whole(bufs, nranks: int, count: int, dtype: int, op: int, compress: int = COMPRESS_NONE,
-                              stream: int = 0) -> None:
+                              cached: int = 0, stream: int = 0) -> None:
     pb, _keep = _ptr_array(bufs)
-    _check(lib.hvdx_ring_allreduce_whole(pb, nranks, count, dtype, op, compress, stream))
+    _check(lib.hvdx_ring_allreduce_whole(pb, nranks, count, dtype, op, compress, cached, stream))
 
 
 def hvdx_ring_allreduce_steps(bufs, nranks: int, count: int, dtype: int, op: int, compress: int = COMPRESS_NONE,

@@ -555,13 +555,13 @@ int hvdx_ring_allgather(void* const* bufs, int nranks, int64_t count, int dtype,
 }
 
 // The whole ring in one launch (arguments already checked, nranks >= 2, count > 0).
-static int run_whole_ring(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
+static int run_whole_ring(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress, bool cached,
                           hipStream_t st) {
   TimedLaunch timed(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, compress, count, st);
   TimedLaunch timed_phase(HVDX_KERNEL_RING_SMALL, -1, nranks, dtype, compress, count, st, -1, true);
   const hipError_t e = hvdx::launch_fold_flat(rank_ptrs(bufs, nranks), ring_args(nranks, count, 0), dtype,
                                               compress == HVDX_COMPRESS_FP16 ? HVDX_FLOAT16 : dtype,
-                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), nranks == 2, st);
+                                              div_mode(op, nranks), vectors_ok(bufs, nranks, nullptr), cached, st);
   return e == hipSuccess ? HVDX_OK : hip_fail(e, "one-launch ring");
 }
 
@@ -573,11 +573,11 @@ int hvdx_ring_allreduce(void* const* bufs, int nranks, int64_t count, int dtype,
   if (nranks == 1)
     return run_phase(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, workspace,
                      workspace_bytes, stream, "hvdx_ring_allreduce");
-  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, nranks == 2, static_cast<hipStream_t>(stream));
 }
 
 int hvdx_ring_allreduce_whole(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
-                              void* stream) {
+                              int cached, void* stream) {
   static const char* what = "hvdx_ring_allreduce_whole";
   if (compress != HVDX_COMPRESS_NONE && compress != HVDX_COMPRESS_FP16)
     return fail(HVDX_ERR_INVALID, "%s: unknown compression %d", what, compress);
@@ -588,7 +588,7 @@ int hvdx_ring_allreduce_whole(void* const* bufs, int nranks, int64_t count, int 
   if (count == 0) return HVDX_OK;
   if (nranks == 1)
     return run_phase(bufs, nranks, count, dtype, op, compress, HVDX_PHASE_REDUCE_SCATTER, nullptr, 0, stream, what);
-  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, cached != 0, static_cast<hipStream_t>(stream));
 }
 
 int hvdx_ring_allreduce_steps(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
@@ -1125,7 +1125,8 @@ int hvdx_ring_allreduce_small(void* const* bufs, int nranks, int64_t count, int 
   int rc = check_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, nullptr, 0, "hvdx_ring_allreduce_small");
   if (rc) return rc;
   if (count == 0 || nranks == 1) return HVDX_OK;  // no messages; AVERAGE divides by 1
-  return run_whole_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, static_cast<hipStream_t>(stream));
+  return run_whole_ring(bufs, nranks, count, dtype, op, HVDX_COMPRESS_NONE, nranks == 2,
+                        static_cast<hipStream_t>(stream));
 }
 
 int hvdx_fold_allreduce(void* const* bufs, int nranks, int64_t count, int dtype, int op, int compress,
@@ -1166,7 +1167,7 @@ int hvdx_ring_allreduce_noalloc(void* const* bufs, int nranks, int64_t count, in
   if (count == 0) return HVDX_OK;
   if (nranks == 1)
     return hvdx_ring_allreduce(bufs, nranks, count, dtype, op, compress, nullptr, 0, stream);
-  return run_whole_ring(bufs, nranks, count, dtype, op, compress, static_cast<hipStream_t>(stream));
+  return run_whole_ring(bufs, nranks, count, dtype, op, compress, nranks == 2, static_cast<hipStream_t>(stream));
 }
 
 static int check_bcast(void* const* bufs, int nranks, int64_t nbytes, int root, const char* what) {

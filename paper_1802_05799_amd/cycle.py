@@ -220,11 +220,14 @@ class FusedAllreduce:
             fused = [i for i, b in enumerate(self.buckets) if not b.direct and b.count > 0]
             direct = [i for i, b in enumerate(self.buckets) if b.direct and b.count > 0]
             alone = self._launched_alone(direct, ptrs)
+            # 2 ranks' loads through the caches where the whole call's tensors fit the Infinity Cache
+            size = _TORCH_DTYPE[self.dtype].itemsize
+            cached = int(n == 2 and sum(self.numel) * size * n <= 272 << 20)
             for i in alone:
                 b = self.buckets[i]
                 bufs, _ = L._ptr_array([p[b.tensors[0]] for p in ptrs])
                 self._cycles.append(_Cycle("ring_small", (i,), L.hvdx_ring_allreduce_whole,
-                                           (bufs, n, b.count, self.dtype, self.op, self.compress)))
+                                           (bufs, n, b.count, self.dtype, self.op, self.compress, cached)))
             for members, kind in ((fused, "cycle_small"), ([i for i in direct if i not in alone], "ring_small")):
                 if not members:
                     continue
@@ -253,13 +256,13 @@ class FusedAllreduce:
 
     def _launched_alone(self, direct, ptrs):
         """Which of the direct buckets run in a launch of their own, over flat rank buffers, and need
-        no entries in a table, whose cutting and upload count in a call made once (allreduce_ of
-        one tensor of 411 MB on 2 ranks: 651 us with a table, 284 us so; on 3: 766, 398; on 8:
-        1415, 1046; repeated calls take the same time).  Those above 64 MiB a rank, whose own
-        launch costs next to nothing, and a last one left.  Not where a rank's start is off a
-        16-byte boundary, which only the table's tiles make up for, and not with more ranks, whose
-        rings take long enough for a table not to count."""
-        if self.nranks > 8:
+        no entries in a table, whose cutting and upload count in a call made once: on 2 and 3
+        ranks, which move little for the elements a table lists (allreduce_ of one tensor of 411
+        MB: 651 us with a table and 284 without, 766 and 398 on 3), those above 64 MiB a rank and
+        a last one left.  A launch more costs a call repeated 3 us (3 ranks, four tensors of 68
+        MB 244 and 256 us, allreduce_ 551 and 303).  Not where a rank's start is off a 16-byte
+        boundary, which only the table's tiles make up for."""
+        if self.nranks > 3:
             return []
         aligned = [i for i in direct if all(p[self.buckets[i].tensors[0]] % 16 == 0 for p in ptrs)]
         size = _TORCH_DTYPE[self.dtype].itemsize

@@ -64,7 +64,7 @@ def test_every_burst(n):
         for offset in (0, 1):
             rows, keep = to_gpu_rows(x, offset)
             hv.hvdx_ring_allreduce_whole([r.data_ptr() for r in rows], n, x.shape[1], NP_TO_HV[x.dtype], hv.AVERAGE,
-                                         hv.COMPRESS_FP16 if compress else hv.COMPRESS_NONE,
+                                         hv.COMPRESS_FP16 if compress else hv.COMPRESS_NONE, offset,  # both loads
                                          torch.cuda.current_stream().cuda_stream)
             assert_bits_equal(from_gpu_rows(rows), oracle_ring(x, "average", compress), f"flat offset={offset}")
         for layout in ("packed", "unalike"):
@@ -176,18 +176,19 @@ ALONE_CASES = [
     # (numel, ranks, threshold, binary16 tensors, compress, elements off a 16-byte start, launches without a table)
     ([17_000_001], 2, 64 << 20, False, False, 0, [0]),  # above 64 MiB a rank
     ([5, 17_000_000, 3001], 3, 1 << 20, False, True, 0, [1]),  # compressed; the others in a fusion buffer
-    ([700, 900, 1000], 5, 2000, False, False, 0, []),  # three direct tensors share a table
-    ([300, 900, 200], 5, 2000, False, False, 0, [1]),  # the only direct one
-    ([900, 200], 4, 1000, True, False, 0, [0]),
-    ([900], 4, 0, False, False, 1, []),  # off a 16-byte start: only a table's tiles make up for it
-    ([900], 9, 0, False, False, 0, []),  # more than 8 ranks: a table does not count
+    ([700, 900, 1000], 3, 2000, False, False, 0, []),  # three direct tensors share a table
+    ([300, 900, 200], 3, 2000, False, False, 0, [1]),  # the only direct one
+    ([900, 200], 2, 1000, True, False, 0, [0]),
+    ([900], 2, 0, False, False, 1, []),  # off a 16-byte start: only a table's tiles make up for it
+    ([900], 4, 0, False, False, 0, []),  # more ranks: a table does not count
+    ([17_000_000, 60_000_000], 2, 64 << 20, False, False, 0, [0, 1]),  # past the Infinity Cache together
 ]
 
 
 @pytest.mark.parametrize("case", range(len(ALONE_CASES)))
 def test_direct_tensors_in_launches_of_their_own(case):
-    """A direct tensor above 64 MiB a rank, or the last one, needs no table cut and uploaded (a
-    call made once pays for it): same bits as in a table."""
+    """On 2 or 3 ranks a direct tensor above 64 MiB a rank, or the last one, needs no table cut and
+    uploaded (a call made once pays for it): same bits as in a table."""
     numel, n, threshold, half, compress, off, want_alone = ALONE_CASES[case]
     say(f"direct tensors alone, case {case}")
     rng = np.random.default_rng(5400 + case)

@@ -30,7 +30,7 @@ def in_steps(x, op, compress):
 def without_workspace(call, x, op, compress):
     n, count = x.shape
     r = rows(x)
-    call([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress, torch.cuda.current_stream().cuda_stream)
+    call([t.data_ptr() for t in r], n, count, hv.FLOAT32, op, compress, stream=torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return np.stack([t.cpu().numpy() for t in r])
 
