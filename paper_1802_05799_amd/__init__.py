@@ -105,10 +105,10 @@ class TensorBroadcast:
     consistent initial variables), every tensor of the list in one chain: a call runs it
     for the whole list, in one launch (hvdx_broadcast_tensors_placed); step() runs one of
     its 2N-2 steps, over the tensors laid end to end at 16-byte aligned starts, `total`
-    bytes in all.  Bytes are copied, not interpreted: tensor t must have the same byte count on every rank (any dtype), be
-    contiguous, on one GPU, and share memory with no other tensor.  The descriptor
-    tables are uploaded once (asynchronously, from pinned memory); the tensors must stay
-    allocated and in place."""
+    bytes in all.  Bytes are copied, not interpreted: tensor t must have the same byte
+    count on every rank (any dtype), be contiguous, on one GPU, and share memory with no
+    other tensor.  The descriptor tables are uploaded once (asynchronously, from pinned
+    memory); the tensors must stay allocated and in place."""
 
     def __init__(self, per_rank):
         import numpy as np
