@@ -202,6 +202,11 @@ def test_direct_tensors_in_launches_of_their_own(case):
     assert alone == want_alone
     assert len(ar.kernel_sequence()) == len(ar._cycles) <= 2
     want = native.allreduce(host, "average", compress=compress, threshold=threshold)
-    for r in range(n):
-        for t in range(len(numel)):
-            assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"rank {r} tensor {t}")
+    graph = ar.capture()
+    for replay in range(4):  # the call, then replays on fresh inputs
+        for r in range(n):
+            for t in range(len(numel)):
+                assert_bits_equal(dev[r][t].cpu().numpy(), want[r][t], f"replay {replay} rank {r} tensor {t}")
+                dev[r][t].copy_(torch.from_numpy(host[r][t]))
+        graph.replay()
+        torch.cuda.synchronize()
